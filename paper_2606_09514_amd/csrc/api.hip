@@ -96,10 +96,18 @@ const char* layer_base(const Model& M, const void* kv, int l) {
     return (const char*)kv + (size_t)l * per_layer * elem_size(c);
 }
 
-// Position chunks per (sequence, KV head): enough workgroups to cover the
-// chip (about 2048 over the launch), chunk lengths a multiple (at least two)
-// of the rows one workgroup block reads, at most kAttnMaxChunks chunks, or
-// `cap` (at least 1) when that is smaller.
+// Position chunks per (sequence, KV head): at most 512 workgroups over the
+// launch (two per CU) and at most 32 chunks per row (or the 256 workgroups
+// that give every CU one), chunk lengths a multiple (at least two) of the
+// rows one workgroup block reads, at most kAttnMaxChunks chunks, or `cap`
+// (at least 1) when that is smaller.  More and shorter chunks cost more than
+// they balance: every workgroup splits its queries and fills its pipeline
+// again, and the merge reads every partial (2048 workgroups against 512,
+// 8-block models, one box: Llama-8B shape B = 1, 30011 rows 570 -> 546 us a
+// step, B = 4, 8000 rows 1245 -> 1188, B = 16, 4000 rows 1135 -> 1084;
+// Qwen-7B shape B = 40, 3000 rows 1587 -> 1515; 13B MHA shape B = 1, 16000
+// rows 541 -> 523).  The count is rounded down: 520 workgroups would leave
+// most CUs waiting for the eight that run three (13B, B = 1: 560 us).
 constexpr int kAttnMinBlocks = 2;   // workgroup blocks per chunk, at least
 
 void attn_chunks(const Model& M, int n_rows, int max_pos, int* chunks, int* chunk_len,
@@ -116,7 +124,9 @@ void attn_chunks(const Model& M, int n_rows, int max_pos, int* chunks, int* chun
         *chunks = 1;
         return;
     }
-    int want = (2048 + pairs - 1) / pairs;
+    int want = 512 / pairs;
+    const int most = 256 / pairs > 32 ? 256 / pairs : 32;
+    if (want > most) want = most;
     if (want > blocks) want = blocks;
     if (want > kAttnMaxChunks) want = kAttnMaxChunks;
     if (want > cap) want = cap;

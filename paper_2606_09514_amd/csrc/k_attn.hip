@@ -901,11 +901,20 @@ void attn_prefill_kernel(AttnArgs a) {
 
 
 // Merge of the chunk partials of one (routed sequence, query head): the
-// chunk maxima and sums go through LDS once, then every thread folds one
-// output element over the chunks in chunk order with coalesced reads.
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
+// chunk maxima and sums go through LDS once, then the workgroup's NT threads
+// fold the output elements: NT / hd groups of threads take every (NT / hd)th
+// chunk each, in chunk order with coalesced reads, and the groups' sums meet
+// in LDS in group order.  A group's additions are a serial chain of loads, so
+// many chunks take more groups: 1024 threads above kMergeWideChunks chunks
+// (235 chunks of 128 rows, Llama-8B shape, B = 1: 12.6 us with half of 256
+// threads adding all of them).
+constexpr int kMergeWideChunks = 32;
+template <int NT>
+__global__ __launch_bounds__(NT) void attn_combine_kernel(AttnArgs a) {
+    constexpr int NW = NT / kWave;
     __shared__ float s_w[kAttnMaxChunks];
-    __shared__ float s_red[4];
+    __shared__ float s_max[NW], s_sum[NW];
+    __shared__ float s_acc[NT];
     const int i = blockIdx.y;
     if (!a.rows.exact && i >= *a.rows.cnt) return;
     const int b = row_seq(a.rows, i);
@@ -917,24 +926,40 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
     const float mc = tid < a.chunks ? pp[tid * pstride + a.hd] : -INFINITY;
     const float lc = tid < a.chunks ? pp[tid * pstride + a.hd + 1] : 0.f;
     float M = wave_max(mc);
-    if (lane == 0) s_red[wave] = M;
+    if (lane == 0) s_max[wave] = M;
     __syncthreads();
-    M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+    M = s_max[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_max[w]);
     const float wc = scale_of(mc, M);
     if (tid < a.chunks) s_w[tid] = wc;
-    float L = tid < a.chunks ? lc * wc : 0.f;
-    L = wave_sum(L);
-    __syncthreads();                      // s_red reads above are done
-    if (lane == 0) s_red[wave] = L;
+    const float Lw = wave_sum(tid < a.chunks ? lc * wc : 0.f);
+    if (lane == 0) s_sum[wave] = Lw;
     __syncthreads();
-    L = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
-    for (int e = tid; e < a.hd; e += 256) {
-        float A = 0.f;
+    const int groups = NT / a.hd, grp = tid / a.hd, e = tid - grp * a.hd;
+    float A = 0.f;
 #pragma unroll 8
-        for (int q = 0; q < a.chunks; ++q) A += pp[q * pstride + e] * s_w[q];
-        const int col = head * a.hd + e;
-        if (a.xb_out) store_split(a.xb_out, xbs_index(i, col, a.nq * a.hd, 0), A / L);
-        else a.o[(size_t)b * a.nq * a.hd + col] = A / L;
+    for (int q = grp; q < a.chunks; q += groups) A += pp[q * pstride + e] * s_w[q];
+    s_acc[tid] = A;
+    __syncthreads();
+    if (grp > 0) return;
+    float L = 0.f;
+    for (int w = 0; w < NW; ++w) L += s_sum[w];
+    for (int q = 1; q < groups; ++q) A += s_acc[q * a.hd + e];
+    const int col = head * a.hd + e;
+    if (a.xb_out) store_split(a.xb_out, xbs_index(i, col, a.nq * a.hd, 0), A / L);
+    else a.o[(size_t)b * a.nq * a.hd + col] = A / L;
+}
+
+template <int NT>
+static void launch_combine(const AttnArgs& a, hipStream_t s) {
+    const dim3 grid(a.nq, a.rows.n_max);
+    LaunchEvents& ev = tl_merge_events;
+    if (ev.start) {
+        hipExtLaunchKernelGGL(attn_combine_kernel<NT>, grid, dim3(NT), 0, s, ev.start, ev.stop, 0, a);
+        ev.start = ev.stop = nullptr;
+    } else {
+        attn_combine_kernel<NT><<<grid, NT, 0, s>>>(a);
     }
 }
 
@@ -1002,14 +1027,8 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.chunks == 1) return hipSuccess;   // the score kernel wrote o
-    LaunchEvents& ev = tl_merge_events;
-    if (ev.start) {
-        hipExtLaunchKernelGGL(attn_combine_kernel, dim3(a.nq, a.rows.n_max), dim3(256), 0, s,
-                              ev.start, ev.stop, 0, a);
-        ev.start = ev.stop = nullptr;
-    } else {
-        attn_combine_kernel<<<dim3(a.nq, a.rows.n_max), 256, 0, s>>>(a);
-    }
+    if (a.chunks > kMergeWideChunks) launch_combine<1024>(a, s);
+    else launch_combine<256>(a, s);
     return hipGetLastError();
 }
 
