@@ -418,8 +418,13 @@ hipError_t launch_route(const Model& M, const void* kc, const void* vc, uint8_t*
 
 // ---------------------------------------------------------------- prefill
 
-// One workgroup per (sequence, block): zero rows 0..len-1 of a skipped
-// block (16-byte stores) and, with an execution map, its entries.
+// Zero rows 0..len-1 of a skipped block (16-byte stores) and, with an
+// execution map, the block's entries: the gridDim.z workgroups of a
+// (block, sequence) share its rows.  Bound by the stores (33.5 MB for one
+// skipped block of a 2048-token prompt, Llama-8B shape; eight stores of each
+// cache per thread keep the CUs busy: one workgroup per (block, sequence)
+// took 144 us for three such blocks, now 10 us).
+constexpr int kFillPerThread = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void prefill_fill_kernel(void* kc, void* vc, uint8_t* exec,
                                                            const uint8_t* mask, const int32_t* len,
@@ -429,13 +434,14 @@ __global__ __launch_bounds__(256) void prefill_fill_kernel(void* kc, void* vc, u
     const int n = len[b];
     const int Lm = L - 1 - S;
     const bool run = l < S || l == L - 1 || mask[(size_t)b * Lm + (l - S)];
+    const int t0 = blockIdx.z * 256 + threadIdx.x, step = gridDim.z * 256;
     if (exec)
-        for (int t = threadIdx.x; t < n; t += 256) exec[((size_t)l * bcap + b) * T_cap + t] = run;
+        for (int t = t0; t < n; t += step) exec[((size_t)l * bcap + b) * T_cap + t] = run;
     if (run) return;
     constexpr int V = St<T>::V;
     const int per_row = hd / V;
     const size_t layer = (size_t)l * bcap * nkv * T_cap * hd;
-    for (int t = threadIdx.x; t < nkv * n * per_row; t += 256) {
+    for (int t = t0; t < nkv * n * per_row; t += step) {
         const int g = t / (n * per_row), r = t - g * n * per_row;
         const int row = r / per_row, e = (r - row * per_row) * V;
         const size_t at = layer + (((size_t)b * nkv + g) * T_cap + row) * hd + e;
@@ -448,8 +454,10 @@ hipError_t launch_prefill_fill(const Model& M, void* kc, void* vc, uint8_t* exec
                                const uint8_t* mask, const int32_t* len, int B, int max_len,
                                hipStream_t s) {
     const buddy_config& c = M.cfg;
-    (void)max_len;
-    const dim3 grid(c.n_layers, B);
+    const int per_row = c.head_dim / (c.dtype == BUDDY_BF16 ? 8 : 4);
+    const size_t vecs = (size_t)c.n_kv_heads * max_len * per_row;
+    const size_t want = (vecs + 256 * kFillPerThread - 1) / (256 * kFillPerThread);
+    const dim3 grid(c.n_layers, B, want < 1024 ? (unsigned)want : 1024);
     if (c.dtype == BUDDY_BF16)
         prefill_fill_kernel<bf16_t><<<grid, 256, 0, s>>>(kc, vc, exec, mask, len, start_layer(c),
                                                          c.n_layers, c.max_ctx, c.max_batch,
