@@ -5,6 +5,8 @@ import pytest
 import torch
 
 from _gpu import Pair
+from oracle import group_by_route
+from paper_2606_09514_amd import lib as blib
 from paper_2606_09514_amd import synth
 from test_gpu_parity import gqa_shape, one_step_all
 
@@ -26,3 +28,22 @@ def test_chunk_merge_widths(case):
     hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
     x = synth.hidden_inputs(1, P.cfg["d_model"], seed=202).numpy()
     print(case, one_step_all(P, hk, hv, [T - 1], [1], x))
+
+
+@pytest.mark.parametrize("B,n", [(63, 64), (64, 65), (255, 128), (256, 129), (257, 64), (511, 65), (1000, 255)])
+def test_group_widths(B, n):
+    """Path grouping at the edges of its word counts (64 blocks a word), of a wavefront's and
+    of the one-workgroup launch's sequences; starts past the last group stay untouched."""
+    rng = np.random.default_rng(B + n)
+    m = rng.integers(0, 2, size=(max(1, B // 3), n)).astype(np.uint8)[rng.integers(0, max(1, B // 3), size=B)]
+    m[B // 2:, : n - 1] = m[0, : n - 1]   # long runs of routes that differ in the last block only
+    m = np.ascontiguousarray(m * 200)
+    perm = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    starts = torch.full((B + 1,), -7, dtype=torch.int32, device="cuda")
+    ng = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    blib.group_by_route(torch.from_numpy(m).cuda(), perm, starts, ng)
+    ref_perm, ref_starts = group_by_route(m)
+    g = int(ng.item())
+    assert g == len(ref_starts) - 1
+    assert np.array_equal(perm.cpu().numpy(), ref_perm)
+    assert np.array_equal(starts.cpu().numpy(), np.concatenate([ref_starts, np.full(B - g, -7)]))
