@@ -152,14 +152,14 @@ bool uses_gemm(const Model& M, const Rows& rows, int batch, int K, int tok_T) {
 
 // Whether a projection of K inputs over `batch` rows takes the MFMA path.
 bool uses_mfma(const Model& M, const Rows& rows, int batch, int K, int tok_T) {
-    return M.cfg.dtype == BUDDY_BF16 && batch > kGemvMaxRows && K % 128 == 0 &&
+    return M.cfg.dtype == BUDDY_BF16 && mfma_batch(M.cfg, batch) && K % 128 == 0 &&
            !uses_gemm(M, rows, batch, K, tok_T);
 }
 
-// A routed projection: the GEMV for batches of up to kGemvMaxRows sequences
-// (or fp32 weights), the MFMA path beyond.  The choice depends on the batch,
-// not on how many sequences a block routes, so a sequence's arithmetic does
-// not depend on the routes of the others or on the launch policy.
+// A routed projection: the GEMV for small batches (mfma_batch) or fp32
+// weights, the MFMA path beyond.  The choice depends on the batch, not on how
+// many sequences a block routes, so a sequence's arithmetic does not depend
+// on the routes of the others or on the launch policy.
 // fold: the MFMA path's residual add goes to the partial buffer for the next
 // staging to add (the caller has checked that the buffer holds the rows):
 // fold_part, or the handle's K-split buffer.
@@ -240,6 +240,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     g.vc = (void*)layer_base(M, kv->v, l);
     g.tok_T = bf.tok_T;
     g.XB = bf.xb; g.ldxb = bf.xb_ld;
+    g.parts = xb_parts(batch);
 
     // RMSNorm + QKV projection + rotary + KV append
     g.W = w.wqkv; g.N = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim; g.K = c.d_model;
@@ -264,6 +265,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     a.T = c.max_ctx; a.hd = c.head_dim; a.nq = c.n_heads; a.nkv = c.n_kv_heads;
     a.bcap = c.max_batch; a.pos = M.ws.pos; a.pos_u = pos_u; a.rows = rows;
     a.tok_T = bf.tok_T;
+    a.parts = g.parts;
     if (bf.tok_T > 0) {
         // prompt tokens: one chunk per row (no merge; the partials are
         // sized for decode rows only)
@@ -280,8 +282,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
         attn_chunks(M, rows.n_max, max_pos, &a.chunks, &a.chunk_len,
                     pooled && !exec ? M.ws.max_pool_splits : kAttnMaxChunks);
         // decode rows on the MFMA path: o goes straight to the O
-        // projection's staging, split into bf16 high and low parts as its
-        // staging would
+        // projection's staging, split into bf16 parts as its staging would
         if (uses_mfma(M, rows, batch, qdim, 0)) a.xb_out = bf.xb;
     }
     a.part = M.ws.part; a.max_chunks = M.ws.max_chunks;
@@ -571,7 +572,7 @@ buddy_status buddy_model_create(const buddy_config* cfg, const buddy_layer_weigh
     // batch or a short prompt's tokens
     size_t part_elems = 0;
     const int part_rows = Bc > kGemmMinRows ? (int)Bc : kGemmMinRows;
-    if (c.dtype == BUDDY_BF16 && Bc > (size_t)kGemvMaxRows) {
+    if (c.dtype == BUDDY_BF16 && mfma_batch(c, (int)Bc)) {
         size_t splits = mfma_splits(EPI_ADD, c.d_model, c.d_ffn);
         const size_t so = mfma_fold_splits(c.d_model, (int)qdim);   // the O projection's
         if (so > splits) splits = so;
@@ -582,7 +583,7 @@ buddy_status buddy_model_create(const buddy_config* cfg, const buddy_layer_weigh
     // MFMA path with the down projection K-split): one buffer per block
     size_t down_elems = 0;
     M.ws.down_splits = 0;
-    if (c.dtype == BUDDY_BF16 && Bc > (size_t)kGemvMaxRows && Lm > 0) {
+    if (c.dtype == BUDDY_BF16 && mfma_batch(c, (int)Bc) && Lm > 0) {
         const int sd = mfma_splits(EPI_ADD, c.d_model, c.d_ffn);
         if (sd > 1 && mfma_fold_splits(c.d_model, c.d_ffn) == sd) {
             M.ws.down_splits = sd;

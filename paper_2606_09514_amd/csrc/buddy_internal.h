@@ -354,8 +354,8 @@ struct GemvArgs {
     // pooled first-layer features of variant ctx (buddy_router_ctx) built
     // from the pool's split partial sums, then h
     const float* pool_part; int pool_splits, pool_max_splits; const float* h; int d; int ctx;
-    // MFMA path: compact activation rows, split high / low bf16 fragments
-    // (xbs_index; the prefill's tiled GEMM: one bf16 fragment, xb_index)
+    // MFMA path: compact activation rows as bf16 parts in fragment order
+    // (store_staged; the prefill's tiled GEMM: one bf16 fragment, xb_index)
     bf16_t* XB; int ldxb;
     // PRO_RMSNORM on the MFMA path: K-split partial sums of the preceding
     // residual-add projection, [split][row capacity][K] by launch row, that
@@ -376,8 +376,9 @@ struct GemvArgs {
     int part_cap;
     // EPI_SWIGLU (tiled GEMM and MFMA paths): the outputs in the next
     // projection's staging order with K = f (its staged input) instead of Y:
-    // xb_index bf16 for the tiled GEMM, xbs_index split for the MFMA path
+    // xb_index bf16 for the tiled GEMM, store_staged's for the MFMA path
     bf16_t* xb_out;
+    int parts;                         // MFMA path: layout of XB and xb_out (xb_parts)
 };
 
 // Element (row i, column k) of activations in B-operand fragment order for
@@ -408,12 +409,39 @@ __device__ __forceinline__ float split_rest(float v, uint32_t hi_bits16) {
     return (r - r) == 0.f ? r : 0.f;
 }
 
-// Stores v at high-part index `at` (xbs_index with part 0) and its low part
-// one fragment (512 elements) further.
-__device__ __forceinline__ void store_split(bf16_t* xb, size_t at, float v) {
+// Packed activations of small batches: the 16 columns of one B operand hold
+// all parts of every row, row i's part p (0 the rounding of the value, 1 and
+// 2 the roundings of the remainders) in column i parts + p, so that one
+// fragment and one MFMA per k-step serve up to 16 / parts rows.  Three parts
+// hold the fp32 value's 24 bits (up to 5 rows), two its first 16 (up to 8).
+__host__ __device__ inline size_t xbp_index(int col, int k) {
+    return (((size_t)(k >> 5) * 64 + col + 16 * ((k >> 3) & 3)) << 3) + (k & 7);
+}
+
+// Parts per row of the packed layout for a batch (decode sequences, or the
+// tokens of a short prompt), 0 for the split layout.  Up to 5 rows three
+// parts: the GEMV those batches took before keeps fp32 activations, and so
+// must this.  From 6 to 8 rows the split layout's two parts in one fragment
+// instead of two half-empty ones.
+constexpr int kPack3Rows = 5, kPack2Rows = 8;
+inline int xb_parts(int batch) { return batch <= kPack3Rows ? 3 : batch <= kPack2Rows ? 2 : 0; }
+
+// Stores value v of launch row i, column k of a K-column MFMA input, in the
+// layout of `parts` (xb_parts).
+__device__ __forceinline__ void store_staged(bf16_t* xb, int parts, int i, int k, int K, float v) {
     const bf16_t hi = f2bf(v);
+    const float r1 = split_rest(v, hi);
+    const bf16_t mid = f2bf(r1);
+    if (parts == 0) {
+        const size_t at = xbs_index(i, k, K, 0);
+        xb[at] = hi;
+        xb[at + 512] = mid;
+        return;
+    }
+    const size_t at = xbp_index(i * parts, k);   // the next column is 8 elements on
     xb[at] = hi;
-    xb[at + 512] = f2bf(split_rest(v, hi));
+    xb[at + 8] = mid;
+    if (parts == 3) xb[at + 16] = f2bf(split_rest(r1, mid));
 }
 
 // Pooled inputs of the router context: 2 n_kv hd for [mean K | mean V],
@@ -475,8 +503,26 @@ hipError_t launch_prep(int pro, const GemvArgs& g, hipStream_t s);
 // projections (null: no split).
 hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, hipStream_t s);
 constexpr int kGemmMinRows = 64;
-// Routed rows above which a bf16 projection takes the MFMA path.
+// Whether the bf16 projections of a batch take the MFMA path (decode
+// sequences, or the tokens of a short prompt); fixed by the batch and the
+// model, so that a sequence's arithmetic never depends on the routes of the
+// others.  One sequence streams faster through the GEMV (Llama-8B shape:
+// gate/up 36 us against 39, and no staging kernels).  From two to four the
+// GEMV passes every weight by each row in turn (Qwen-7B shape, three rows:
+// gate/up 87 us and down 95, MFMA 50 and 30), while the MFMA path adds two
+// staging launches a block: it pays once rows x weight bytes of a block reach
+// kMfmaRowBytes (8-block models, GEMV against MFMA, us a step: Llama-8B,
+// 436 MB a block, B = 2 654 / 640, B = 4 1109 / 768; 201 MB a block B = 2
+// 383 / 480, B = 3 604 / 489; 150 MB B = 3 518 / 569, B = 4 611 / 575; 90 MB
+// B = 4 415 / 492).
 constexpr int kGemvMaxRows = 4;
+constexpr size_t kMfmaRowBytes = 580u * 1000 * 1000;
+inline bool mfma_batch(const buddy_config& c, int batch) {
+    if (batch > kGemvMaxRows || batch < 2) return batch > kGemvMaxRows;
+    const size_t d = c.d_model, hd = c.head_dim;
+    const size_t rows = (size_t)(2 * c.n_heads + 2 * c.n_kv_heads) * hd + 3 * (size_t)c.d_ffn;
+    return 2 * d * rows * batch >= kMfmaRowBytes;
+}
 // MFMA path: workgroups below which a launch takes smaller weight tiles per
 // workgroup or splits K; the most K splits.
 constexpr int kMfmaMinGrid = 384;
@@ -533,9 +579,10 @@ struct AttnArgs {
     const uint8_t* exec;                // this block's execution map [bcap][T], or null
     int tok_T;                          // > 0: rows are prompt tokens (slot_pos)
     // o of launch row i in the O projection's staging order instead of fp32
-    // o (decode rows: split high / low, xbs_index; prompt tokens of the
-    // prefill attention kernel: bf16, xb_index, with K = nq hd); or null
+    // o (decode rows: store_staged in the layout of xb_parts; prompt tokens of
+    // the prefill attention kernel: bf16, xb_index, with K = nq hd); or null
     bf16_t* xb_out;
+    int parts;
     // prompt tokens on the prefill attention kernel: groups of up to 128 / G
     // consecutive tokens of one prompt, (first row index, count) pairs; one
     // workgroup per (KV head, group) (null: one per row)

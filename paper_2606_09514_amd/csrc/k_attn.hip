@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
         }
         if (a.chunks == 1) {
             const int col = (g * G + h) * a.hd + e;
-            if (a.xb_out) store_split(a.xb_out, xbs_index(i, col, a.nq * a.hd, 0), A / L);
+            if (a.xb_out) store_staged(a.xb_out, a.parts, i, col, a.nq * a.hd, A / L);
             else a.o[(size_t)b * a.nq * a.hd + col] = A / L;
         } else {
             float* pp = a.part + (((size_t)b * a.nq + g * G + h) * a.max_chunks + c) * pstride;
@@ -638,7 +638,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POOL ? 2 : 
         }
         if (a.chunks == 1) {
             const int col = (g * G + h) * HD + e;
-            if (a.xb_out) store_split(a.xb_out, xbs_index(i, col, a.nq * HD, 0), A / L);
+            if (a.xb_out) store_staged(a.xb_out, a.parts, i, col, a.nq * HD, A / L);
             else a.o[(size_t)b * a.nq * HD + col] = A / L;
         } else {
             float* pp = a.part + (((size_t)b * a.nq + g * G + h) * a.max_chunks + c) * pstride;
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnArgs a) {
     for (int w = 0; w < NW; ++w) L += s_sum[w];
     for (int q = 1; q < groups; ++q) A += s_acc[q * a.hd + e];
     const int col = head * a.hd + e;
-    if (a.xb_out) store_split(a.xb_out, xbs_index(i, col, a.nq * a.hd, 0), A / L);
+    if (a.xb_out) store_staged(a.xb_out, a.parts, i, col, a.nq * a.hd, A / L);
     else a.o[(size_t)b * a.nq * a.hd + col] = A / L;
 }
 

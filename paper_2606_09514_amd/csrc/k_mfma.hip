@@ -1,10 +1,11 @@
 // MFMA path of the routed projections (gfx950, bf16 weights), used for
-// batches of more than four sequences: the projection is then a real dense
+// batches beyond the GEMV's (mfma_batch): the projection is then a real dense
 // contraction over the routed rows.
 //
 //  prep_kernel  writes the routed rows in MFMA operand order (row i of the
 //               launch is sequence idx[i]) as bf16 high and low parts
-//               (xbs_index): RMSNorm and gain folded in (PRO_RMSNORM), the
+//               (xbs_index; three or two parts in one fragment for small
+//               batches, xbp_index): RMSNorm and gain folded in (PRO_RMSNORM), the
 //               router context built from the pool's split sums (PRO_POOL), or
 //               a plain conversion (PRO_NONE).  Inputs staged by their
 //               producer (PRO_STAGED: the attention output, the SwiGLU output)
@@ -133,17 +134,27 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(GemvArgs g, int n_ho
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] *= inv * gv[q];
         }
-        // high parts, then the low parts from the exact remainders
-        uint32_t hi[4], lo[4];
+        // high parts, then the further parts from the exact remainders
+        uint32_t hi[4], mid[4];
+        float r[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             hi[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
-            lo[q] = pack_bf16x2(split_rest(v[2 * q], hi[q] & 0xffffu),
-                                split_rest(v[2 * q + 1], hi[q] >> 16));
+            r[2 * q] = split_rest(v[2 * q], hi[q] & 0xffffu);
+            r[2 * q + 1] = split_rest(v[2 * q + 1], hi[q] >> 16);
+            mid[q] = pack_bf16x2(r[2 * q], r[2 * q + 1]);
         }
-        const size_t at = xbs_index(i, k, K, 0);
+        const size_t at = g.parts ? xbp_index(i * g.parts, k) : xbs_index(i, k, K, 0);
         *reinterpret_cast<uint4*>(g.XB + at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        *reinterpret_cast<uint4*>(g.XB + at + 512) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        *reinterpret_cast<uint4*>(g.XB + at + (g.parts ? 8 : 512)) = make_uint4(mid[0], mid[1], mid[2], mid[3]);
+        if (g.parts == 3) {
+            uint32_t lo[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                lo[q] = pack_bf16x2(split_rest(r[2 * q], mid[q] & 0xffffu),
+                                    split_rest(r[2 * q + 1], mid[q] >> 16));
+            *reinterpret_cast<uint4*>(g.XB + at + 16) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        }
     }
 }
 
@@ -187,10 +198,15 @@ __host__ __device__ constexpr int mfma_lds_bytes(int rt, int nt, int gt, int kr 
 // weight loads are pending).  The k-steps enter the accumulators in the
 // same order for either round length, so the sums are identical bit for bit.
 // KR = 4 needs a multiple of four k-steps per wavefront (no partial round).
-template <int EPI, int NT, int RT, int KR = 2>
+// PACK: the packed activations of a small batch (xbp_index; NT = 1): one
+// fragment and one MFMA per weight tile and k-step; a row's sum is that of
+// its g.parts columns, the smallest part first.
+template <int EPI, int NT, int RT, int KR = 2, bool PACK = false>
 __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_host, float* part,
                                                    int fold) {
     static_assert(KR == 2 || KR == 4, "rounds of two or four k-steps");
+    static_assert(!PACK || NT == 1, "packed rows fill one column tile");
+    constexpr int FR = PACK ? 1 : 2;          // fragments per column tile and k-step
     constexpr bool kPaired = EPI == EPI_SWIGLU || EPI == EPI_QKV;
     constexpr int GT = kPaired ? 2 : 1;       // weight tiles per epilogue group
     constexpr int NG = RT / GT;               // epilogue groups (16 units or rows each)
@@ -266,7 +282,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         const bf16_t* Bp[NT];
 #pragma unroll
         for (int c = 0; c < NT; ++c)
-            Bp[c] = g.XB + (((size_t)((j0 >> 4) + min(c, nct - 1)) * S + kw) * 128 + lane) * 8;
+            Bp[c] = g.XB + (((size_t)((j0 >> 4) + min(c, nct - 1)) * S + kw) * (64 * FR) + lane) * 8;
 
         f32x4_t acc[RT][NT];
 #pragma unroll
@@ -279,16 +295,19 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         for (int r = 0; r < nr; ++r) {
             const int buf = r & 1;
             const bool half = KR == 2 && 2 * r + 1 >= sw;
-            u32x4_t bv[KR][2][NT];   // [k-step u][high, low][column tile]
+            u32x4_t bv[KR][FR][NT];   // [k-step u][high, low][column tile]
 #pragma unroll
             for (int u = 0; u < KR; ++u)
 #pragma unroll
                 for (int c = 0; c < NT; ++c) {
-                    const bf16_t* bp = Bp[c] + 1024 * (KR * r + (half ? 0 : u));
+                    const bf16_t* bp = Bp[c] + 512 * FR * (KR * r + (half ? 0 : u));
                     // reads data no kernel writes while this one runs: no memory clobber
-                    asm volatile("global_load_dwordx4 %0, %2, off\n\t"
-                                 "global_load_dwordx4 %1, %2, off offset:1024"
-                                 : "=&v"(bv[u][0][c]), "=&v"(bv[u][1][c]) : "v"(bp));
+                    if constexpr (PACK)
+                        asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(bv[u][0][c]) : "v"(bp));
+                    else
+                        asm volatile("global_load_dwordx4 %0, %2, off\n\t"
+                                     "global_load_dwordx4 %1, %2, off offset:1024"
+                                     : "=&v"(bv[u][0][c]), "=&v"(bv[u][FR - 1][c]) : "v"(bp));
                 }
             if (r + 1 < nr) {
                 issue_a(r + 1, buf ^ 1);
@@ -326,15 +345,14 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
             if constexpr (KR == 2) {
                 const uint32_t keep = half ? 0u : ~0u;
 #pragma unroll
-                for (int c = 0; c < NT; ++c) {
-                    bv[1][0][c] &= keep;
-                    bv[1][1][c] &= keep;
-                }
+                for (int c = 0; c < NT; ++c)
+#pragma unroll
+                    for (int p = 0; p < FR; ++p) bv[1][p][c] &= keep;
             }
 #pragma unroll
             for (int u = 0; u < KR; ++u)
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int p = 0; p < FR; ++p)
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -347,6 +365,16 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         // per epilogue group: reduce the four K-slices through LDS, then the
         // epilogue on the finished sums (wavefront order fixed: deterministic)
         const int ncols = min(NT * 16, n - j0);
+        auto sum4 = [&](int t, int il, int c) {
+            return (s_red[0][t][il][c] + s_red[1][t][il][c]) + (s_red[2][t][il][c] + s_red[3][t][il][c]);
+        };
+        auto row_sum = [&](int t, int il, int j) {
+            if constexpr (!PACK) return sum4(t, il, j);
+            const int c = j * g.parts;
+            float v = sum4(t, il, c + 1);
+            if (g.parts == 3) v += sum4(t, il, c + 2);
+            return v + sum4(t, il, c);
+        };
 #pragma unroll
         for (int q = 0; q < NG; ++q) {
             __syncthreads();   // the previous group's epilogue is done with s_red
@@ -363,9 +391,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                     const int il = p & 15, j = p >> 4;
                     const int uu = u0 + 16 * q + il;
                     if (uu >= units) continue;
-                    part[((size_t)blockIdx.y * g.part_cap + j0 + j) * units + uu] =
-                        (s_red[0][0][il][j] + s_red[1][0][il][j]) +
-                        (s_red[2][0][il][j] + s_red[3][0][il][j]);
+                    part[((size_t)blockIdx.y * g.part_cap + j0 + j) * units + uu] = row_sum(0, il, j);
                 }
                 continue;
             }
@@ -377,8 +403,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
 #pragma unroll
                     for (int t = 0; t < GT; ++t)
                         part[part_index(blockIdx.y, GT, t, units, uu, g.rows.n_max, j0 + j)] =
-                            (s_red[0][t][il][j] + s_red[1][t][il][j]) +
-                            (s_red[2][t][il][j] + s_red[3][t][il][j]);
+                            row_sum(t, il, j);
                 }
                 continue;
             }
@@ -387,13 +412,11 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                 const int uu = u0 + 16 * q + il;
                 if (uu >= units) continue;
                 const int b = row_seq(g.rows, j0 + j);
-                const float v0 = (s_red[0][0][il][j] + s_red[1][0][il][j]) +
-                                 (s_red[2][0][il][j] + s_red[3][0][il][j]);
+                const float v0 = row_sum(0, il, j);
                 if (kPaired) {
-                    const float v1 = (s_red[0][GT - 1][il][j] + s_red[1][GT - 1][il][j]) +
-                                     (s_red[2][GT - 1][il][j] + s_red[3][GT - 1][il][j]);
+                    const float v1 = row_sum(GT - 1, il, j);
                     if (EPI == EPI_SWIGLU && g.xb_out) {   // the down projection's staged input
-                        store_split(g.xb_out, xbs_index(j0 + j, uu, g.f, 0), swiglu(v0, v1));
+                        store_staged(g.xb_out, g.parts, j0 + j, uu, g.f, swiglu(v0, v1));
                         continue;
                     }
                     int r0, r1;
@@ -443,7 +466,7 @@ __global__ __launch_bounds__(256) void split_add_kernel(GemvArgs g, int units, i
 
 // One instantiation's launch; LDS beyond the 64 KB default (eight weight
 // tiles per workgroup, or four-k-step rounds) is allowed once per device.
-template <int EPI, int NT, int RT, int KR>
+template <int EPI, int NT, int RT, int KR, bool PACK = false>
 static hipError_t launch_tiles(dim3 grid, const GemvArgs& g, int units, int n_host, float* part,
                                int fold, hipStream_t s) {
     constexpr int kGT = EPI == EPI_SWIGLU || EPI == EPI_QKV ? 2 : 1;
@@ -456,13 +479,13 @@ static hipError_t launch_tiles(dim3 grid, const GemvArgs& g, int units, int n_ho
         if (e != hipSuccess) return e;
         const uint64_t bit = 1ull << (dev & 63);
         if (!(attr_set.load(std::memory_order_relaxed) & bit)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_kernel<EPI, NT, RT, KR>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_kernel<EPI, NT, RT, KR, PACK>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
             attr_set.fetch_or(bit, std::memory_order_relaxed);
         }
     }
-    launch_main(mfma_kernel<EPI, NT, RT, KR>, grid, dim3(256), (uint32_t)lds, s, g, units, n_host,
+    launch_main(mfma_kernel<EPI, NT, RT, KR, PACK>, grid, dim3(256), (uint32_t)lds, s, g, units, n_host,
                 part, fold);
     return hipGetLastError();
 }
@@ -475,7 +498,8 @@ static hipError_t launch_mfma_rounds(const GemvArgs& g, int units, int n_host, i
     const dim3 grid((units + per - 1) / per, splits);
     const int tiles = (g.rows.n_max + 15) / 16;
     hipError_t e;
-    if (tiles <= 1) e = launch_tiles<EPI, 1, RT, KR>(grid, g, units, n_host, part, fold, s);
+    if (g.parts) e = launch_tiles<EPI, 1, RT, KR, true>(grid, g, units, n_host, part, fold, s);
+    else if (tiles <= 1) e = launch_tiles<EPI, 1, RT, KR>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 2) e = launch_tiles<EPI, 2, RT, KR>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 3) e = launch_tiles<EPI, 3, RT, KR>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 4) e = launch_tiles<EPI, 4, RT, KR>(grid, g, units, n_host, part, fold, s);

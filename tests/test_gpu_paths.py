@@ -47,3 +47,43 @@ def test_group_widths(B, n):
     assert g == len(ref_starts) - 1
     assert np.array_equal(perm.cpu().numpy(), ref_perm)
     assert np.array_equal(starts.cpu().numpy(), np.concatenate([ref_starts, np.full(B - g, -7)]))
+
+
+@pytest.mark.parametrize("B", [3, 4])
+def test_small_batch_rule(B):
+    """Both sides of the rule that takes batches of two to four sequences to the MFMA path
+    (rows x weight bytes of a block: 159 MB here, 478 and 637 MB), blocks routed by one to
+    all sequences.  Both keep fp32 activations: the same bound."""
+    shape = dict(n_layers=5, d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=11264,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    T = 200
+    P = Pair(shape, "bf16", T, B, seed=220, omega=0.1)
+    g = torch.Generator().manual_seed(221)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    x = synth.hidden_inputs(B, 2048, seed=222).numpy()
+    rep = one_step_all(P, hk, hv, [T - 1, 150, 60, 199][:B], [1, 3, 2, 0][:B], x)
+    print(B, rep)
+    assert rep["max_hidden_err"] < 1e-5
+
+
+@pytest.mark.parametrize("B", [5, 6, 8, 9])
+def test_packed_activation_parts(B):
+    """The batches at the edges of the activation layouts: three parts (24 bits) packed up to
+    5 sequences, two packed up to 8, split tiles beyond; K-split O and down projections,
+    deferred sums, rows that a block does not route.  A misplaced part leaves bf16's 8 bits
+    (errors of 1e-3); with 24 bits the hidden state is 1e-7 to 2e-7 off, with 16 about 5e-7:
+    ten times that is allowed."""
+    shape = dict(n_layers=6, d_model=256, n_heads=4, n_kv_heads=1, head_dim=128, d_ffn=1024,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    T = 600
+    P = Pair(shape, "bf16", T, B, seed=210, omega=0.1)
+    g = torch.Generator().manual_seed(211 + B)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    pos = [T - 1 - 37 * b for b in range(B)]
+    ks = [b % (P.L_mid + 1) for b in range(B)]
+    x = synth.hidden_inputs(B, 256, seed=212).numpy()
+    rep = one_step_all(P, hk, hv, pos, ks, x)
+    print(B, rep)
+    assert rep["max_hidden_err"] < (2e-6 if B <= 5 else 5e-6)
