@@ -201,8 +201,9 @@ buddy_status buddy_pool_route(buddy_model* m, const buddy_kv* kv, const int32_t*
  * h_new, B, scores_out and stream as for buddy_pool_route.  Every buffer
  * the kernels need beyond the inputs and outputs (positions, pool partial
  * sums, the Decision Module's hidden activations, scores) lives in a scratch
- * array of 8 MiB that the library holds once per device for the life of the
- * process; no part of it needs to start at zero.  That limits a call to
+ * array that the library holds once per device for the life of the
+ * process (12 MiB, 8 of them counted here; no part of it needs to start at
+ * zero).  That limits a call to
  * pieces of 4 B bytes (three of them), 4, 4 B L_mid + 4, 4 B dm_hidden and
  * 8 B n_kv_heads head_dim splits bytes, each rounded up to 256, totalling at
  * most 8 MiB, where splits, the pool's position splits, is 1 with

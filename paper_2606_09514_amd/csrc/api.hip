@@ -393,14 +393,16 @@ buddy_status run_planner(Model& M, const buddy_kv* kv, const float* h, int B, in
     g.pool_max_splits = M.ws.max_pool_splits; g.h = h; g.d = c.d_model;
     // the Decision Module keeps fp32 activations at every batch size: routes
     // are decided on these scores
-    if ((e = launch_gemv(c.dtype, PRO_POOL, EPI_BIAS_ACT, g, s)) != hipSuccess)
-        return fail_device(M, e, "dm_hidden");
+    e = dm_uses_mfma(c, B, g.N, g.K) ? launch_dm(g, M.ws.dm_part, s)
+                                     : launch_gemv(c.dtype, PRO_POOL, EPI_BIAS_ACT, g, s);
+    if (e != hipSuccess) return fail_device(M, e, "dm_hidden");
     // the Budget Predictor's first layer on the same router context
     if (predict) {
         g.W = M.pred.w1; g.N = M.pred.hidden; g.bias = M.pred.b1;
         g.Y = M.pred_a; g.ldy = M.pred.hidden;
-        if ((e = launch_gemv(c.dtype, PRO_POOL, EPI_BIAS_ACT, g, s)) != hipSuccess)
-            return fail_device(M, e, "predictor_hidden");
+        e = dm_uses_mfma(c, B, g.N, g.K) ? launch_dm(g, pred_part(M), s)
+                                         : launch_gemv(c.dtype, PRO_POOL, EPI_BIAS_ACT, g, s);
+        if (e != hipSuccess) return fail_device(M, e, "predictor_hidden");
     }
     return BUDDY_OK;
 }
@@ -500,8 +502,14 @@ buddy_status check_step_host(const Model& M, const int32_t* pos, int B, int* max
 // copy at its own address until the process ends).  Host code never uses
 // the array's name as an address; it takes the device address that
 // hipGetSymbolAddress returns for the current device.
+// Behind the 8 MiB that the call's documented limit counts lie the K-slice
+// sums of the Decision Module's first layer (at most 256 x 16 x 128, or
+// kMaxBatch x kDmMaxHidden, floats).
 constexpr size_t kNoAllocScratchBytes = (size_t)8 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+constexpr size_t kNoAllocPartBytes = (size_t)4 << 20;
+static_assert(kNoAllocPartBytes >= sizeof(float) * kMaxBatch * kDmMaxHidden &&
+              kNoAllocPartBytes >= sizeof(float) * 256 * 16 * kDmUnits, "first-layer sums");
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocPartBytes];
 
 constexpr int kScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -598,6 +606,7 @@ buddy_status buddy_model_create(const buddy_config* cfg, const buddy_layer_weigh
         {(void**)&W.n_all, 4}, {(void**)&W.idx, Lm * Bc * 4 + 4}, {(void**)&W.cnt, Lm * 4 + 4},
         {(void**)&W.mask, Bc * Lm + 1}, {(void**)&W.scores, Bc * Lm * 4 + 4},
         {(void**)&W.z, Bc * din * 4}, {(void**)&W.a, Bc * c.dm_hidden * 4},
+        {(void**)&W.dm_part, Bc > 1 ? dm_part_elems(c.max_batch, c.dm_hidden) * 4 : 0},
         {(void**)&W.q, Bc * qdim * 4}, {(void**)&W.o, Bc * qdim * 4},
         {(void**)&W.m, Bc * c.d_ffn * 4},
         {(void**)&W.part, Bc * c.n_heads * max_chunks * (hd + 2) * 4},
@@ -725,6 +734,7 @@ buddy_status buddy_pool_route_noalloc(const buddy_config* cfg, const buddy_dm_we
     if (e != hipSuccess) return BUDDY_EDEVICE;
     size_t off = 0;
     for (const Piece& q : pieces) { *q.dst = (char*)base + off; off += align_up(q.bytes); }
+    W.dm_part = (float*)((char*)base + kNoAllocScratchBytes);
     W.max_pool_splits = splits;          // partial stride: this call's split count
     hipStream_t s = (hipStream_t)stream;
     StepArgs a;
@@ -775,7 +785,8 @@ buddy_status buddy_set_budget_predictor(buddy_model* h, const buddy_predictor_we
     M.pred_a = nullptr;
     memset(&M.pred, 0, sizeof(M.pred));
     if (!p) return BUDDY_OK;
-    e = hipMalloc((void**)&M.pred_a, (size_t)M.cfg.max_batch * p->hidden * sizeof(float));
+    e = hipMalloc((void**)&M.pred_a, ((size_t)M.cfg.max_batch * p->hidden +
+                                      dm_part_elems(M.cfg.max_batch, p->hidden)) * sizeof(float));
     if (e != hipSuccess) { M.pred_a = nullptr; return BUDDY_ENOMEM; }
     M.pred = *p;
     return BUDDY_OK;

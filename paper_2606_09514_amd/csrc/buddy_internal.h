@@ -138,6 +138,7 @@ struct Workspace {
     float* scores;       // [max_batch][L-2]
     float* z;            // [max_batch][din]  router context
     float* a;            // [max_batch][dm_hidden]
+    float* dm_part;      // K-slice sums of the router's first layer (launch_dm)
     float* q;            // [max_batch][n_heads hd]  rotated queries
     float* o;            // [max_batch][n_heads hd]  attention output
     float* m;            // [max_batch][d_ffn]       SwiGLU output
@@ -217,7 +218,7 @@ struct Model {
     buddy_layer_weights* layers;  // host array of device pointers
     buddy_dm_weights dm;
     buddy_predictor_weights pred;  // Budget Predictor head (pred.hidden == 0: none)
-    float* pred_a;                 // [max_batch][pred.hidden] its hidden activations
+    float* pred_a;                 // [max_batch][pred.hidden] its hidden activations, then its K-slice sums
     // prefill workspace, grown on demand to pf_rows prompt-token rows (one
     // allocation): queries, attention outputs, SwiGLU outputs, MFMA staging,
     // per-block token lists [L][rows], prompt lengths, last-token hidden rows
@@ -232,6 +233,9 @@ struct Model {
     int device;
     char last_error[256];
 };
+
+// K-slice sums of the Budget Predictor's first layer (behind its activations).
+inline float* pred_part(const Model& M) { return M.pred_a + (size_t)M.cfg.max_batch * M.pred.hidden; }
 
 // Per-step host values handed to the device through kernel arguments.
 struct StepArgs {
@@ -486,6 +490,34 @@ __device__ __forceinline__ float4 pooled_feature4(const GemvArgs& g, int b, int 
     return v;
 }
 hipError_t launch_gemv(int dtype, int pro, int epi, const GemvArgs& g, hipStream_t s);
+// The router's first layers over a batch on the MFMA (bf16 weights): the
+// sums W z_b of PRO_POOL's context in fp32, per K slice, part[slice][b][unit],
+// for every sequence of the batch (g.rows is the identity); the router kernel
+// adds the slices, the bias and the activation.
+hipError_t launch_dm(const GemvArgs& g, float* part, hipStream_t s);
+constexpr int kDmUnits = 128;      // hidden units of a workgroup
+constexpr int kDmMaxHidden = 4096; // the router kernel holds them in LDS
+// K slices: until the grid has about 256 workgroups, at least four k-steps
+// (one per wavefront) each.  Fixed by the batch and the shape.
+inline int dm_slices(int B, int H, int K) {
+    const int tiles = (H + kDmUnits - 1) / kDmUnits * ((B + 15) / 16), steps = K / 32;
+    int want = 256 / tiles;
+    if (want > steps / 4) want = steps / 4;
+    if (want < 1) want = 1;
+    const int per = (steps + want - 1) / want;
+    return (steps + per - 1) / per;
+}
+// Whether a first layer of H units over K inputs takes it for B sequences
+// (one sequence's GEMV launch has 128 workgroups and folds its pool splits
+// with all of them: 6.5 us at the Llama-8B shape).
+inline bool dm_uses_mfma(const buddy_config& c, int B, int H, int K) {
+    return c.dtype == BUDDY_BF16 && B > 1 && H <= kDmMaxHidden && K % 32 == 0;
+}
+// Floats of part: slices x tiles <= 256, or one slice.
+inline size_t dm_part_elems(int max_batch, int H) {
+    const size_t few = (size_t)256 * 16 * kDmUnits, one = (size_t)max_batch * H;
+    return few > one ? few : one;
+}
 // MFMA path (bf16 weights, K a multiple of 128): prep of the compact bf16
 // rows, then the MFMA projection with the same epilogues.  part: fp32
 // workspace of mfma_part_elems for the K-split projections.

@@ -23,6 +23,7 @@
 // Partial results always travel through a kernel boundary; no kernel here
 // synchronises workgroups (device-wide fences are costly across the XCDs).
 #include "buddy_internal.h"
+#include "epilogue.h"
 
 namespace buddy {
 
@@ -214,7 +215,10 @@ __device__ __forceinline__ bool beats(float sj, int j, float si, int i) {
 }
 
 struct RouteParams {
+    // first layer's activations [B][H], or (part != null) its K-slice sums
+    // [slices][B][H], to which bias b1 and activation are still to come
     const float* a; int H;
+    const float* part; int slices; const void* b1; int act;
     const void* w2; const void* b2; const float* prior; float omega;
     int Lm, B;
     int S, L;                         // start layer (routable blocks S..L-2), blocks
@@ -230,6 +234,7 @@ struct RouteParams {
     // Budget Predictor: hidden activations [B][Hp] (null: budgets from the
     // step arguments), output layer, and the optional outputs
     const float* pa; int Hp; const void* pw2; const void* pb2;
+    const float* ppart; int pslices; const void* pb1;   // as part, slices, b1
     int32_t* k_out; float* logits_out;
 };
 
@@ -259,11 +264,28 @@ __device__ __forceinline__ void output_layer(const void* w, const void* bias, co
     }
 }
 
+// First-layer activations of sequence b from the K-slice sums (in slice
+// order), into LDS.
 template <typename T>
+__device__ __forceinline__ void first_layer(const float* part, int slices, int B, int b, const void* b1,
+                                            int act, int H, float* s_a) {
+    for (int h = threadIdx.x; h < H; h += 1024) {
+        const float* pp = part + (size_t)b * H + h;
+        float v = 0.f;
+#pragma unroll 8
+        for (int c = 0; c < slices; ++c) v += pp[(size_t)c * B * H];
+        s_a[h] = act_fn(v + St<T>::get((const T*)b1, h), act);
+    }
+    __syncthreads();
+}
+
+// SLICES: some first layer comes as K-slice sums.
+template <typename T, bool SLICES>
 __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, StepArgs sa) {
     __shared__ float s_sc[256];
     __shared__ uint8_t s_mask[256];
     __shared__ int s_k;
+    __shared__ float s_a[SLICES ? kDmMaxHidden : 1];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int Lm = p.Lm;
@@ -271,7 +293,12 @@ __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, StepArgs sa)
     // Budget Predictor (Sec. 4.4): k = 1 + argmax of the policy logits (the
     // softmax is monotone), smaller k on equal logits, NaN never chosen
     if (p.pa) {
-        output_layer<T>(p.pw2, p.pb2, p.pa + (size_t)b * p.Hp, p.Hp, Lm, wave, lane, s_sc);
+        if (SLICES && p.ppart) {
+            first_layer<T>(p.ppart, p.pslices, p.B, b, p.pb1, p.act, p.Hp, s_a);
+            output_layer<T>(p.pw2, p.pb2, s_a, p.Hp, Lm, wave, lane, s_sc);
+        } else {
+            output_layer<T>(p.pw2, p.pb2, p.pa + (size_t)b * p.Hp, p.Hp, Lm, wave, lane, s_sc);
+        }
         __syncthreads();
         if (tid < Lm && p.logits_out) p.logits_out[(size_t)b * Lm + tid] = s_sc[tid];
         if (wave == 0) {
@@ -298,7 +325,12 @@ __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, StepArgs sa)
     if (p.route_override) {
         if (tid < Lm) s_mask[tid] = p.route_override[(size_t)b * Lm + tid] != 0;
     } else {
-        output_layer<T>(p.w2, p.b2, p.a + (size_t)b * p.H, p.H, Lm, wave, lane, s_sc);
+        if (SLICES && p.part) {
+            first_layer<T>(p.part, p.slices, p.B, b, p.b1, p.act, p.H, s_a);
+            output_layer<T>(p.w2, p.b2, s_a, p.H, Lm, wave, lane, s_sc);
+        } else {
+            output_layer<T>(p.w2, p.b2, p.a + (size_t)b * p.H, p.H, Lm, wave, lane, s_sc);
+        }
         __syncthreads();
         if (p.prior && tid < Lm) s_sc[tid] += p.omega * p.prior[tid];
         __syncthreads();
@@ -407,8 +439,16 @@ hipError_t launch_route(const Model& M, const void* kc, const void* vc, uint8_t*
     p.pa = predict ? M.pred_a : nullptr; p.Hp = M.pred.hidden;
     p.pw2 = M.pred.w2; p.pb2 = M.pred.b2;
     p.k_out = k_out; p.logits_out = logits_out;
-    if (c.dtype == BUDDY_BF16) route_kernel<bf16_t><<<B, 1024, 0, s>>>(p, a);
-    else route_kernel<float><<<B, 1024, 0, s>>>(p, a);
+    const int din = pooled_dim(c.router_ctx, c.n_kv_heads, c.head_dim) + c.d_model;
+    const bool dm = !route_override && dm_uses_mfma(c, B, c.dm_hidden, din);
+    const bool pdm = predict && dm_uses_mfma(c, B, M.pred.hidden, din);
+    p.part = dm ? M.ws.dm_part : nullptr;
+    p.slices = dm_slices(B, c.dm_hidden, din); p.b1 = M.dm.b1; p.act = c.dm_act;
+    p.ppart = pdm ? pred_part(M) : nullptr;
+    p.pslices = pdm ? dm_slices(B, M.pred.hidden, din) : 0; p.pb1 = M.pred.b1;
+    if (c.dtype == BUDDY_F32) route_kernel<float, false><<<B, 1024, 0, s>>>(p, a);
+    else if (dm || pdm) route_kernel<bf16_t, true><<<B, 1024, 0, s>>>(p, a);
+    else route_kernel<bf16_t, false><<<B, 1024, 0, s>>>(p, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || scores_only || p.Lm == 0 || B == 1) return e;
     compact_kernel<<<1, 256, 0, s>>>(M.ws.mask, p.Lm, B, c.max_batch, M.ws.idx, M.ws.cnt,

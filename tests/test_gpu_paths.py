@@ -87,3 +87,31 @@ def test_packed_activation_parts(B):
     rep = one_step_all(P, hk, hv, pos, ks, x)
     print(B, rep)
     assert rep["max_hidden_err"] < (2e-6 if B <= 5 else 5e-6)
+
+
+@pytest.mark.parametrize("B,H,ctx,d,T", [(2, 8, "kv", 96, 40), (2, 136, "k+v", 96, 3000), (16, 128, "k", 3936, 70),
+                                         (17, 264, "v", 608, 500), (33, 4096, "kv", 352, 90), (3, 4104, "kv", 352, 90),
+                                         (3, 64, "kv", 232, 90), (1, 64, "kv", 96, 90)])
+def test_router_first_layer(B, H, ctx, d, T):
+    """The Decision Module's first layer on the MFMA at the edges of its tiles (units, sequences,
+    K slices and k-steps that do not divide, one to 24 pool splits per row), and the sizes that stay on
+    the GEMV: hidden widths past the router kernel's LDS, inputs that are not whole k-steps, one
+    sequence.  fp32 context on both: the scores' 1e-5; the entry point without a handle gives
+    the same bits."""
+    shape = dict(n_layers=6, d_model=d, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=128,
+                 dm_hidden=H, dm_act="gelu", rope_theta=1e4, rms_eps=1e-5, router_ctx=ctx)
+    P = Pair(shape, "bf16", T, B, seed=230, omega=0.1)
+    g = torch.Generator().manual_seed(231)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    dk, dv = P.upload(hk), P.upload(hv)
+    h = synth.hidden_inputs(B, d, seed=232)
+    pos = [(T - 1 - 13 * b) % T for b in range(B)]
+    scores, again = (torch.zeros((B, P.L_mid), device="cuda") for _ in range(2))
+    P.gpu.pool_route(dk, dv, pos, h.cuda(), scores)
+    blib.pool_route_noalloc(P.cfg, P.Wd["dm"], B, dk, dv, pos, h.cuda(), again)
+    got = scores.cpu().numpy()
+    assert np.array_equal(got, again.cpu().numpy())
+    for b in range(B):
+        ref = P.orc.dm_scores(P.orc.context(hk[0, b], hv[0, b], pos[b], h[b].numpy()))
+        assert np.max(np.abs(got[b] - ref)) <= 1e-5 * max(1.0, float(np.max(np.abs(ref)))), b
