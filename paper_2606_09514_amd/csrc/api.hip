@@ -167,7 +167,7 @@ hipError_t launch_proj(const Model& M, int batch, int pro, int epi, GemvArgs g, 
                        bool fold = false, float* fold_part = nullptr) {
     // prompt tokens of a prefill: the tiled GEMM
     if (uses_gemm(M, g.rows, batch, g.K, g.tok_T))
-        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, s);
+        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, M.pf_rows), s);
     if (uses_mfma(M, g.rows, batch, g.K, g.tok_T))
         return launch_mfma(pro, epi, g,
                            fold_part ? fold_part
@@ -960,7 +960,7 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
         // prompt tokens (high and low parts)
         {(void**)&M.pf_xb, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
         {(void**)&M.pf_xb2, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
-        {(void**)&M.pf_split, 2 * rows * (size_t)c.d_model * 4},
+        {(void**)&M.pf_split, gemm_part_elems(c, rows) * 4},
         {(void**)&M.pf_lists, L * rows * 4}, {(void**)&M.pf_len, (size_t)c.max_batch * 4},
         {(void**)&M.pf_groups, L * rows * 8},
     };

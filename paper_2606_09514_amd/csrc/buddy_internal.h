@@ -225,7 +225,7 @@ struct Model {
     void* pf_base; size_t pf_rows;
     float *pf_q, *pf_o, *pf_m, *pf_hlast;
     bf16_t* pf_xb, *pf_xb2;
-    float* pf_split;               // split-K partial sums [2][rows][d_model]
+    float* pf_split;               // split-K partial sums, gemm_part_elems(rows)
     int32_t *pf_lists, *pf_len, *pf_groups;
     int32_t* pf_hlists;            // host copy of the token lists, then of the groups
     Workspace ws;
@@ -531,10 +531,20 @@ hipError_t launch_mfma(int pro, int epi, const GemvArgs& g, float* part, hipStre
 hipError_t launch_prep(int pro, const GemvArgs& g, hipStream_t s);
 // Tiled MFMA GEMM for many rows (prompt tokens): exact row counts, bf16
 // weights, K a multiple of 64.
-// part: fp32 workspace of 2 x rows x N for the split-K residual-add
-// projections (null: no split).
-hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, hipStream_t s);
+// part: fp32 workspace of part_elems for the split-K sums.
+hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,
+                       hipStream_t s);
 constexpr int kGemmMinRows = 64;
+// Split-K sums of a prefill of `rows` tokens: two splits of the residual-add
+// projections, or for prompts of up to kGemmShortRows tokens up to 49152
+// (splits x weight rows) per token, 128 MB at most.
+constexpr int kGemmShortRows = 1536;
+inline size_t gemm_part_elems(const buddy_config& c, size_t rows) {
+    const size_t two = 2 * rows * c.d_model;
+    size_t few = rows * 49152;
+    if (few > (size_t)32 << 20) few = (size_t)32 << 20;
+    return two > few ? two : few;
+}
 // Whether the bf16 projections of a batch take the MFMA path (decode
 // sequences, or the tokens of a short prompt); fixed by the batch and the
 // model, so that a sequence's arithmetic never depends on the routes of the

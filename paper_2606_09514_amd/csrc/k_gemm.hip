@@ -7,11 +7,18 @@
 // stepping K by 32.  For the two-row kinds (SwiGLU, QKV) the weight rows of
 // a tile are 8 WM TI units: their first rows in the upper half of the row
 // tiles and their second rows in the lower half, and each wavefront holds
-// the first and second rows of the same units.  Two shapes:
+// the first and second rows of the same units.  Three shapes:
 //   128 x 128 (2 x 2 wavefronts of 64 x 64), two workgroups per CU;
 //   256 x 256 (2 x 4 wavefronts of 128 x 64), one workgroup per CU, which
-//     halves the bytes each CU fetches per flop (the loads through the
-//     texture path, not the MFMA, bound the smaller tile).
+//     halves the bytes each CU fetches per flop;
+//   128 x 256 (2 x 4 wavefronts of 64 x 64), one workgroup per CU: the
+//     weights of up to 256 tokens pass once, and twice the grid of the large
+//     tile for the 4096-row projections.
+// With eight wavefronts the two of each SIMD run in antiphase (below).  What
+// bounds the 256 x 256 tile is the MFMA and what does not overlap it: gate/up
+// of a 2048-token prompt (Llama-8B shape, three rounds of tiles) 357 us with
+// the wavefronts in phase, 328 to 338 in antiphase, 1.1 PFLOP/s where a
+// large library product of random bf16 values reaches 1.46 on this card.
 // Both operands pass through LDS in MFMA fragment order, so each wavefront
 // reads a fragment as one conflict-free 16-byte read per lane:
 //   A fragment (row tile rt): 1 KB at rt KB of the step's buffer, lane
@@ -20,8 +27,8 @@
 //     from the activations, which the staging kernel already wrote in
 //     B-operand order (16 rows x 32 k per contiguous KB).
 // Tiles travel straight from memory to LDS (global_load_lds) three K steps
-// ahead of the multiply (four buffers, one barrier per step); each row
-// tile's MFMAs start as soon as its own fragment read has landed.
+// ahead of the multiply (four buffers); in the 128 x 128 tile each row tile's
+// MFMAs start as soon as its own fragment read has landed.
 //   D[i][j] (16 x 16): lane j + 16 (i / 4), element i % 4.
 #include "buddy_internal.h"
 #include "epilogue.h"
@@ -94,6 +101,16 @@ __device__ __forceinline__ void lds_wait(u32x4_t& r, u32x4_t* y) {
                  : "i"(N));
 }
 
+// Every fragment of a step: nothing may read them before this wait.
+template <int TI>
+__device__ __forceinline__ void lds_wait_all(u32x4_t* a, u32x4_t* y) {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(y[0]), "+v"(y[1]), "+v"(y[2]),
+                   "+v"(y[3]));
+    if constexpr (TI == 8)
+        asm volatile("" : "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
+}
+
 // One K step's MFMAs, row tile I onwards: each row tile after its own read
 // (and, for the first, the B fragments') has landed.
 template <int I, int TI, int TJ>
@@ -116,6 +133,8 @@ __device__ __forceinline__ void mfma_rows(f32x4_t (&acc)[TI][TJ], u32x4_t* a, u3
 template <int WM, int WN, int TI, int TJ>
 struct GemmShape {
     static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
+    // eight wavefronts, two per SIMD, one workgroup per CU
+    static constexpr bool kPingPong = kWaves == 8;
     static constexpr int kRowTiles = WM * TI, kColTiles = WN * TJ;
     static constexpr int kRows = 16 * kRowTiles, kCols = 16 * kColTiles;
     static constexpr int kBufBytes = (kRowTiles + kColTiles) * kFragBytes;
@@ -125,6 +144,21 @@ struct GemmShape {
     static_assert(kBufs * kBufBytes <= 128 * 1024, "LDS");
     static_assert(TJ == 4 && (TI == 4 || TI == 8), "wavefront tile");
 };
+
+// Four finished units or rows of a token (launch row col, row id b): SwiGLU
+// outputs as bf16 into the next projection's staging if asked for, one
+// 8-byte store (f % 8 == 0), otherwise the shared epilogues.
+template <int EPI>
+__device__ __forceinline__ void tile_epilogue(const GemvArgs& g, int units, int col, int b, int u,
+                                              const float* v0, const float* v1) {
+    if (EPI == EPI_SWIGLU && g.xb_out) {
+        *reinterpret_cast<uint2*>(g.xb_out + xb_index(col, u, units)) =
+            make_uint2(pack_bf16x2(swiglu(v0[0], v1[0]), swiglu(v0[1], v1[1])),
+                       pack_bf16x2(swiglu(v0[2], v1[2]), swiglu(v0[3], v1[3])));
+        return;
+    }
+    epilogue4<EPI>(g, b, u, v0, v1);
+}
 
 template <int EPI, int WM, int WN, int TI, int TJ>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -201,21 +235,8 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
     constexpr int kSecond = kPaired ? Sh::kRowTiles / 2 - TI / 2 : 0;   // gap to the second rows
     constexpr int F = kFragBytes;
 
-    // At step kb: wait until only the loads of steps kb + 1 and kb + 2 are
-    // outstanding, barrier (every wavefront's loads of step kb have landed
-    // and every wavefront has read step kb - 1's buffer), refill that buffer
-    // with step kb + 3, multiply step kb.
-    issue(0);
-    issue(1);
-    issue(2);
-    for (int kb = 0; kb < nk; ++kb) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
-        // a plain barrier: __syncthreads() would also wait for every load in
-        // flight (its fence covers the direct-to-LDS writes)
-        asm volatile("s_barrier" ::: "memory");
-        issue(kb + 3);
+    auto read_frags = [&](int kb, u32x4_t* a, u32x4_t* bv) {
         const uint32_t sb = (kb % kBufs) * Sh::kBufBytes;
-        u32x4_t a[TI], bv[TJ];
         if constexpr (TI == 4) {
             lds_issue8<0, F, (2 + kSecond) * F, (3 + kSecond) * F>(a_off + sb, b_off + sb, a, bv);
         } else {
@@ -223,65 +244,98 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
             lds_issue4<(4 + kSecond) * F, (5 + kSecond) * F, (6 + kSecond) * F, (7 + kSecond) * F>(
                 a_off + sb, a + 4);
         }
-        mfma_rows<0>(acc, a, bv);
+    };
+    issue(0);
+    issue(1);
+    issue(2);
+    if constexpr (Sh::kPingPong) {
+        // Two wavefronts per SIMD in antiphase: while wavefronts 0 .. 3 (one
+        // per SIMD) multiply a step from registers, wavefronts 4 .. 7 read
+        // their next fragments and issue loads, and the other way round, a
+        // barrier between the phases.  (In phase, both read LDS and then both
+        // multiply: MFMA 44 % busy.)  Early wavefronts read step k in phase 2 k
+        // and multiply it in phase 2 k + 1, late ones a phase later.  The loads
+        // of step k have landed for everyone after the barrier that ends
+        // phase 2 k - 1: each wavefront waits for its own share before it
+        // (early: after multiplying step k - 1; late: after reading it), with
+        // the loads of steps k + 1 and k + 2, issued by then, in flight.
+        // Step k's buffer is refilled with step k + 4's loads by the reads of
+        // step k + 1 (phase 2 k + 2 at the earliest): everyone has read step k
+        // by the end of phase 2 k + 1, its reads waited for before the barrier.
+        const bool late = wave >= 4;
+        __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
+        asm volatile("s_barrier" ::: "memory");
+        if (late) asm volatile("s_barrier" ::: "memory");   // phase 0 is the early wavefronts'
+        for (int kb = 0; kb < nk; ++kb) {
+            u32x4_t a[TI], bv[TJ];
+            read_frags(kb, a, bv);
+            issue(kb + 3);
+            lds_wait_all<TI>(a, bv);
+            if (late) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, a[i]), __builtin_bit_cast(bf16x8_t, bv[j]),
+                        acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            if (!late) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!late) asm volatile("s_barrier" ::: "memory");  // the late wavefronts' last phase
+    } else {
+        // At step kb: wait until only the loads of steps kb + 1 and kb + 2 are
+        // outstanding, barrier (every wavefront's loads of step kb have landed
+        // and every wavefront has read step kb - 1's buffer), refill that
+        // buffer with step kb + 3, multiply step kb.
+        for (int kb = 0; kb < nk; ++kb) {
+            __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
+            // a plain barrier: __syncthreads() would also wait for every load
+            // in flight (its fence covers the direct-to-LDS writes)
+            asm volatile("s_barrier" ::: "memory");
+            issue(kb + 3);
+            u32x4_t a[TI], bv[TJ];
+            read_frags(kb, a, bv);
+            mfma_rows<0>(acc, a, bv);
+        }
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));   // the reloads past the end
 
-    if (part) {   // split K (single-row kinds): 4 consecutive units per lane, one 16-byte store
-        float* pz = part + (size_t)blockIdx.z * n * units;
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            const int col = t0 + 16 * (wn * TJ + j) + (lane & 15);
-            if (col >= n) continue;
-#pragma unroll
-            for (int i = 0; i < TI; ++i) {
-                const int r = u0 + 16 * (wm * TI + i) + 4 * (lane >> 4);
-                if (r < units)
-                    *reinterpret_cast<float4*>(pz + (size_t)col * units + r) =
-                        make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-            }
-        }
-        return;
-    }
-
-    // epilogue from the accumulators: rows 4 (lane / 16) + e of each tile
+    // rows (or units) 4 (lane / 16) .. + 3 of each tile, one column (token) per
+    // lane: four at a time
+    constexpr int NU = kPaired ? TI / 2 : TI;                       // tiles of rows or units
+    const int N = kPaired ? 2 * units : units;
+    float* pz = part + (size_t)blockIdx.z * n * N;
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
         const int col = t0 + 16 * (wn * TJ + j) + (lane & 15);
         if (col >= n) continue;
         const int b = row_seq(g.rows, col);
-        if (EPI == EPI_SWIGLU && g.xb_out) {
-            // SiLU(gate) * up of 4 consecutive units as bf16 into the next
-            // projection's staging: one 8-byte store (f % 8 == 0)
 #pragma unroll
-            for (int i = 0; i < TI / 2; ++i) {
-                const int ub = u0 + 16 * (wm * TI / 2 + i) + 4 * (lane >> 4);
-                if (ub >= units) continue;
-                float m[4];
+        for (int i = 0; i < NU; ++i) {
+            const int u = u0 + 16 * (wm * NU + i) + 4 * (lane >> 4);
+            if (u >= units) continue;                               // units % 4 == 0
+            float v0[4], v1[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) m[e] = swiglu(acc[i][j][e], acc[TI / 2 + i][j][e]);
-                *reinterpret_cast<uint2*>(g.xb_out + xb_index(col, ub, units)) =
-                    make_uint2(pack_bf16x2(m[0], m[1]), pack_bf16x2(m[2], m[3]));
+            for (int e = 0; e < 4; ++e) {
+                v0[e] = acc[i][j][e];
+                v1[e] = kPaired ? acc[TI - NU + i][j][e] : 0.f;
             }
-            continue;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (kPaired) {
-#pragma unroll
-                for (int i = 0; i < TI / 2; ++i) {
-                    const int u = u0 + 16 * (wm * TI / 2 + i) + 4 * (lane >> 4) + e;
-                    if (u >= units) continue;
-                    int r0, r1;
-                    unit_rows<EPI>(g, u, r0, r1);
-                    epilogue<bf16_t, EPI>(g, b, u, r0, r1, acc[i][j][e], acc[TI / 2 + i][j][e]);
-                }
+            if (part) {   // split K: part[split][token][weight row]
+                int r0 = u, r1 = u;
+                if (kPaired) unit_rows<EPI>(g, u, r0, r1);
+                *reinterpret_cast<float4*>(pz + (size_t)col * N + r0) = make_float4(v0[0], v0[1], v0[2], v0[3]);
+                if (kPaired)
+                    *reinterpret_cast<float4*>(pz + (size_t)col * N + r1) = make_float4(v1[0], v1[1], v1[2], v1[3]);
             } else {
-#pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int r = u0 + 16 * (wm * TI + i) + 4 * (lane >> 4) + e;
-                    if (r < units) epilogue1<bf16_t, EPI>(g, b, r, acc[i][j][e]);
-                }
+                tile_epilogue<EPI>(g, units, col, b, u, v0, v1);
             }
         }
     }
@@ -392,6 +446,55 @@ static void gemm_launch(const GemvArgs& g, int units, int n, hipStream_t s, floa
                 0, s, g, units, n, part, ubase);
 }
 
+// Split-K partial sums (part[split][token][weight row]) added in split order,
+// then the epilogue, four units (or rows) of a token per thread.
+template <int EPI>
+__global__ __launch_bounds__(256) void splitk_epi_kernel(GemvArgs g, int units, int n, int splits,
+                                                         const float* part) {
+    constexpr bool kPaired = EPI == EPI_SWIGLU || EPI == EPI_QKV;
+    const int q = units >> 2, N = kPaired ? 2 * units : units;
+    for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < (size_t)n * q;
+         t += (size_t)gridDim.x * 256) {
+        const int col = (int)(t / q), u = 4 * (int)(t - (size_t)col * q);
+        int r0 = u, r1 = u;
+        if (kPaired) unit_rows<EPI>(g, u, r0, r1);
+        float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0;
+#pragma unroll 4
+        for (int z = 0; z < splits; ++z) {
+            const float* pz = part + ((size_t)z * n + col) * N;
+            const float4 a = *reinterpret_cast<const float4*>(pz + r0);
+            s0.x += a.x; s0.y += a.y; s0.z += a.z; s0.w += a.w;
+            if (kPaired) {
+                const float4 b = *reinterpret_cast<const float4*>(pz + r1);
+                s1.x += b.x; s1.y += b.y; s1.z += b.z; s1.w += b.w;
+            }
+        }
+        const float v0[4] = {s0.x, s0.y, s0.z, s0.w}, v1[4] = {s1.x, s1.y, s1.z, s1.w};
+        tile_epilogue<EPI>(g, units, col, row_seq(g.rows, col), u, v0, v1);
+    }
+}
+
+// Tile shapes: weight rows x tokens.
+enum Shape { SH_128 = 0, SH_256 = 1, SH_128x256 = 2 };
+
+template <int EPI>
+static dim3 shape_grid(int shape, int units, int n) {
+    if (shape == SH_256) return gemm_grid<EPI, 2, 4, 8, 4>(units, n);
+    if (shape == SH_128x256) return gemm_grid<EPI, 2, 4, 4, 4>(units, n);
+    return gemm_grid<EPI, 2, 2, 4, 4>(units, n);
+}
+
+// Time of `wgs` workgroups over `steps` K steps, us: rounds over the CUs
+// (128 x 128 tiles run two to a CU) times what a step was measured to take
+// (Llama-8B and Qwen-7B projections, 64 to 3150 tokens).
+static float grid_us(int shape, int wgs, int steps) {
+    if (shape == SH_128) {
+        const int rest = wgs % (2 * kCUs);
+        return steps * (0.69f * (wgs / (2 * kCUs)) + (rest > kCUs ? 0.69f : rest > 0 ? 0.33f : 0.f));
+    }
+    return steps * (shape == SH_256 ? 0.8f : 0.47f) * ((wgs + kCUs - 1) / kCUs);
+}
+
 // The last round of a 256 x 256 grid that does not fill the CUs: the units
 // of the row tiles that fill whole rounds stay on 256 x 256 tiles, and the
 // rest go to a second launch of 128 x 128 tiles when those take one round
@@ -411,67 +514,87 @@ static int gemm_tail_units(int units, int n) {
     return small.x * small.y <= 2 * kCUs ? ubig : units;
 }
 
-// Residual add of the split-K partial sums: Y[row] += part[0] + part[1]
-// (fixed order), four units per thread.
-__global__ __launch_bounds__(256) void splitk_add_kernel(GemvArgs g, int units, int n,
-                                                         const float* part) {
-    const int q = units >> 2;
-    for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < (size_t)n * q;
-         t += (size_t)gridDim.x * 256) {
-        const int col = (int)(t / q), r = 4 * (int)(t - (size_t)col * q);
-        const float4 a = *reinterpret_cast<const float4*>(part + (size_t)col * units + r);
-        const float4 b = *reinterpret_cast<const float4*>(part + ((size_t)n + col) * units + r);
-        float* y = g.Y + (size_t)row_seq(g.rows, col) * g.ldy + r;
-        float4 v = *reinterpret_cast<float4*>(y);
-        v.x += a.x + b.x; v.y += a.y + b.y; v.z += a.z + b.z; v.w += a.w + b.w;
-        *reinterpret_cast<float4*>(y) = v;
-    }
-}
-
-// Tile choice (automatic): 256 x 256 where it still gives the CUs two
-// rounds of workgroups, else 128 x 128 (two per CU).  A 256 x 128 tile with
-// one wavefront per SIMD was slower than 128 x 128 on the 4096-row
-// projections (measured).
+// The projection on one tile shape with K in `splits` parts (1: no partial
+// sums), the split sums' epilogue behind it; tail: 256 x 256 tiles with a
+// last round on 128 x 128 ones (gemm_tail_units).
 template <int EPI>
-static hipError_t launch_gemm_epi(const GemvArgs& g, int units, int tile, float* part,
-                                  hipStream_t s) {
-    const int n = g.rows.n_max;
-    const dim3 big = gemm_grid<EPI, 2, 4, 8, 4>(units, n);
-    // split K in two for residual-add projections whose 256 x 256 grid would
-    // leave CUs idle but fills them when doubled (O and down at prefill sizes)
-    const bool split_ok = EPI == EPI_ADD && part && (g.K / kTileK) % 2 == 0 && units % 4 == 0;
-    const bool split = split_ok && (tile == BUDDY_GEMM_TILE_256_SPLIT ||
-                                    (tile == BUDDY_GEMM_TILE_AUTO && big.x * big.y < 2 * kCUs &&
-                                     2 * big.x * big.y >= kCUs));
-    if (split) {
-        gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s, part, 2);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const size_t work = (size_t)n * (units / 4);
-        const int grid = (int)((work + 255) / 256 < 4096 ? (work + 255) / 256 : 4096);
-        splitk_add_kernel<<<grid, 256, 0, s>>>(g, units, n, part);
-    } else if (tile == BUDDY_GEMM_TILE_256 || tile == BUDDY_GEMM_TILE_256_SPLIT) {
-        gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s);
-    } else if (tile == BUDDY_GEMM_TILE_AUTO && big.x * big.y >= 2 * kCUs) {
-        const int ubig = gemm_tail_units<EPI>(units, n);
-        gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s, nullptr, 1, 0, ubig);
+static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int units, int n, float* part,
+                               hipStream_t s, bool tail = false) {
+    if (splits == 1) part = nullptr;
+    if (shape == SH_256) {
+        const int ubig = tail ? gemm_tail_units<EPI>(units, n) : units;
+        gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s, part, splits, 0, ubig);
         if (ubig < units) gemm_launch<EPI, 2, 2, 4, 4>(g, units, n, s, nullptr, 1, ubig);
+    } else if (shape == SH_128x256) {
+        gemm_launch<EPI, 2, 4, 4, 4>(g, units, n, s, part, splits);
     } else {
-        gemm_launch<EPI, 2, 2, 4, 4>(g, units, n, s);
+        gemm_launch<EPI, 2, 2, 4, 4>(g, units, n, s, part, splits);
     }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    const size_t work = (size_t)n * (units / 4);
+    const int grid = (int)((work + 255) / 256 < 4096 ? (work + 255) / 256 : 4096);
+    splitk_epi_kernel<EPI><<<grid, 256, 0, s>>>(g, units, n, splits, part);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, hipStream_t s) {
+// Automatic choice: the tile and K split of least estimated time.  Short
+// prompts (up to kGemmShortRows tokens) leave most CUs without a tile, so
+// their K may split up to eight ways for every kind, as far as the partial
+// buffer holds the sums (197 tokens, Llama-8B shape, with the sums' launch:
+// O 62 -> 24 us, down 184 -> 47, QKV 67 -> 32, gate/up on 128 x 256 tiles
+// 102 -> 81 against 128 x 128 tiles unsplit; 900 tokens, 6 blocks 3040 ->
+// 2257, 13B MHA shape, 1500 tokens, 4 blocks 4960 -> 3480); longer ones split only the residual adds in two, where that fills
+// the CUs.  Adding split sums costs their write and read (about 5 TB/s) and a
+// launch.
+template <int EPI>
+static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t part_elems, hipStream_t s) {
+    const int n = g.rows.n_max, steps = g.K / kTileK;
+    const size_t N = EPI == EPI_ADD ? units : 2 * units;
+    const bool few = n <= kGemmShortRows;
+    int shape = SH_128, splits = 1;
+    float best = 0.f;
+    for (int sh : {SH_128, SH_256, SH_128x256})
+        for (int z = 1; z <= 8; z *= 2) {
+            const dim3 grid = shape_grid<EPI>(sh, units, n);
+            const int wgs = grid.x * grid.y;
+            if (z > 1 && (!part || steps % z || steps / z < 8 || z * n * N > part_elems)) break;
+            if (z > 1 && !few && (EPI != EPI_ADD || sh != SH_256 || z > 2 || 2 * wgs < kCUs)) break;
+            float us = grid_us(sh, wgs * z, steps / z);
+            if (z > 1) us += 4.f + (float)z * n * N * 8.f / 5e6f;
+            if (sh == SH_256 && z == 1) {
+                const int ubig = gemm_tail_units<EPI>(units, n);
+                if (ubig < units) {
+                    const dim3 small = gemm_grid<EPI, 2, 2, 4, 4>(units - ubig, n);
+                    us = grid_us(sh, wgs / kCUs * kCUs, steps) + grid_us(SH_128, small.x * small.y, steps);
+                }
+            }
+            if (best == 0.f || us < best) { best = us; shape = sh; splits = z; }
+        }
+    return launch_shape<EPI>(shape, splits, g, units, n, part, s, true);
+}
+
+template <int EPI>
+static hipError_t launch_gemm_epi(const GemvArgs& g, int units, int tile, float* part,
+                                  size_t part_elems, hipStream_t s) {
+    const int n = g.rows.n_max;
+    if (tile == BUDDY_GEMM_TILE_AUTO) return launch_auto<EPI>(g, units, part, part_elems, s);
+    if (tile == BUDDY_GEMM_TILE_128) return launch_shape<EPI>(SH_128, 1, g, units, n, nullptr, s);
+    const bool split = tile == BUDDY_GEMM_TILE_256_SPLIT && EPI == EPI_ADD && part && (g.K / kTileK) % 2 == 0;
+    return launch_shape<EPI>(SH_256, split ? 2 : 1, g, units, n, part, s);
+}
+
+hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,
+                       hipStream_t s) {
     if (pro != PRO_STAGED) {
         hipError_t e = launch_prep_tiles(pro, g, s);
         if (e != hipSuccess) return e;
     }
     if (epi == EPI_QKV)
-        return launch_gemm_epi<EPI_QKV>(g, (g.nq + 2 * g.nkv) * (g.hd / 2), tile, nullptr, s);
-    if (epi == EPI_SWIGLU) return launch_gemm_epi<EPI_SWIGLU>(g, g.f, tile, nullptr, s);
-    if (epi == EPI_BIAS_ACT) return launch_gemm_epi<EPI_BIAS_ACT>(g, g.N, tile, nullptr, s);
-    return launch_gemm_epi<EPI_ADD>(g, g.N, tile, part, s);
+        return launch_gemm_epi<EPI_QKV>(g, (g.nq + 2 * g.nkv) * (g.hd / 2), tile, part, part_elems, s);
+    if (epi == EPI_SWIGLU) return launch_gemm_epi<EPI_SWIGLU>(g, g.f, tile, part, part_elems, s);
+    if (epi != EPI_ADD) return hipErrorInvalidValue;
+    return launch_gemm_epi<EPI_ADD>(g, g.N, tile, part, part_elems, s);
 }
 
 }  // namespace buddy

@@ -8,7 +8,7 @@ from _gpu import Pair
 from oracle import group_by_route
 from paper_2606_09514_amd import lib as blib
 from paper_2606_09514_amd import synth
-from test_gpu_parity import gqa_shape, one_step_all
+from test_gpu_parity import check_prefill, gpu_prefill, gqa_shape, one_step_all
 
 pytestmark = pytest.mark.gpu
 
@@ -115,3 +115,27 @@ def test_router_first_layer(B, H, ctx, d, T):
     for b in range(B):
         ref = P.orc.dm_scores(P.orc.context(hk[0, b], hv[0, b], pos[b], h[b].numpy()))
         assert np.max(np.abs(got[b] - ref)) <= 1e-5 * max(1.0, float(np.max(np.abs(ref)))), b
+
+
+@pytest.mark.parametrize("lens", [[64], [127], [129], [200, 57], [300, 215], [900, 90]])
+def test_prefill_short_prompts(lens):
+    """The tiled GEMM's automatic choices for short prompts: 128 x 128, 128 x 256 and
+    256 x 256 tiles with K split up to eight ways for every kind of projection (rotary and
+    cache append, SwiGLU, residual add behind the split sums), ragged last tiles, blocks run
+    by one prompt only.  Against the oracle, and against the unsplit 128 x 128 tile: the same
+    products summed in another order, each then rounded to bf16 for the next projection
+    (2^-9 a rounding; 1e-2 of the largest output allowed)."""
+    shape = dict(n_layers=4, d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, d_ffn=2304,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    T = max(lens)
+    P = Pair(shape, "bf16", T, len(lens), seed=240, omega=0.1)
+    ks = [1, 2][:len(lens)]
+    if T <= 300:
+        check_prefill(P, lens, ks, T, seed=241)
+    auto = gpu_prefill(P, lens, ks, T, seed=241)
+    P.gpu.set_gemm_tile(blib.GEMM_TILE_128)
+    plain = gpu_prefill(P, lens, ks, T, seed=241)
+    assert np.array_equal(auto[1], plain[1])
+    for b, n in enumerate(lens):
+        a, p = auto[0][b, :n], plain[0][b, :n]
+        assert np.max(np.abs(a - p)) <= 1e-2 * np.max(np.abs(p))
