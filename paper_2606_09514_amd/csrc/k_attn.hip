@@ -908,7 +908,9 @@ void attn_prefill_kernel(AttnArgs a) {
 // many chunks take more groups: 1024 threads above kMergeWideChunks chunks
 // (235 chunks of 128 rows, Llama-8B shape, B = 1: 12.6 us with half of 256
 // threads adding all of them).
-constexpr int kMergeWideChunks = 32;
+// Up to kMergeOneGroup chunks one group adds them all: two loads fewer in the
+// chain do not pay for a barrier (Llama-8B shape, 11 chunks: about 1 us more).
+constexpr int kMergeWideChunks = 32, kMergeOneGroup = 16;
 template <int NT>
 __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnArgs a) {
     constexpr int NW = NT / kWave;
@@ -936,13 +938,17 @@ __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnArgs a) {
     const float Lw = wave_sum(tid < a.chunks ? lc * wc : 0.f);
     if (lane == 0) s_sum[wave] = Lw;
     __syncthreads();
-    const int groups = NT / a.hd, grp = tid / a.hd, e = tid - grp * a.hd;
+    const int groups = a.chunks > kMergeOneGroup ? NT / a.hd : 1;
+    const int grp = tid / a.hd, e = tid - grp * a.hd;
+    if (grp >= groups) return;            // whole wavefronts
     float A = 0.f;
 #pragma unroll 8
     for (int q = grp; q < a.chunks; q += groups) A += pp[q * pstride + e] * s_w[q];
-    s_acc[tid] = A;
-    __syncthreads();
-    if (grp > 0) return;
+    if (groups > 1) {
+        s_acc[tid] = A;
+        __syncthreads();
+        if (grp > 0) return;
+    }
     float L = 0.f;
     for (int w = 0; w < NW; ++w) L += s_sum[w];
     for (int q = 1; q < groups; ++q) A += s_acc[q * a.hd + e];
