@@ -162,12 +162,14 @@ bool uses_mfma(const Model& M, const Rows& rows, int batch, int K, int tok_T) {
 // on the routes of the others or on the launch policy.
 // fold: the MFMA path's residual add goes to the partial buffer for the next
 // staging to add (the caller has checked that the buffer holds the rows):
-// fold_part, or the handle's K-split buffer.
+// fold_part, or the handle's K-split buffer.  gemm_fold: the same for the
+// tiled GEMM, whose splits it receives.
 hipError_t launch_proj(const Model& M, int batch, int pro, int epi, GemvArgs g, hipStream_t s,
-                       bool fold = false, float* fold_part = nullptr) {
+                       bool fold = false, float* fold_part = nullptr, int* gemm_fold = nullptr) {
     // prompt tokens of a prefill: the tiled GEMM
     if (uses_gemm(M, g.rows, batch, g.K, g.tok_T))
-        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, M.pf_rows), s);
+        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, M.pf_rows), s,
+                           gemm_fold);
     if (uses_mfma(M, g.rows, batch, g.K, g.tok_T))
         return launch_mfma(pro, epi, g,
                            fold_part ? fold_part
@@ -312,9 +314,12 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     g.W = w.wo; g.N = c.d_model; g.K = qdim; g.X = bf.o; g.ldx = qdim; g.gain = nullptr;
     g.Y = hidden; g.ldy = c.d_model;
     g.part_cap = rows.n_max;
+    // prompt tokens: the same when both projections take the tiled GEMM
+    const bool o_gemm = uses_gemm(M, rows, batch, qdim, bf.tok_T) && uses_gemm(M, rows, batch, c.d_model, bf.tok_T);
+    int o_splits = 1;
     if ((e = mark(M, BUDDY_KERNEL_O_PROJ, l, false, s)) != hipSuccess ||
-        (e = launch_proj(M, batch, a.xb_out ? PRO_STAGED : PRO_NONE, EPI_ADD, g, s, o_fold)) !=
-            hipSuccess ||
+        (e = launch_proj(M, batch, a.xb_out ? PRO_STAGED : PRO_NONE, EPI_ADD, g, s, o_fold, nullptr,
+                         o_gemm ? &o_splits : nullptr)) != hipSuccess ||
         (e = mark(M, BUDDY_KERNEL_O_PROJ, l, true, s)) != hipSuccess)
         return fail_device(M, e, "o_proj");
 
@@ -331,6 +336,10 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     if (o_fold) {
         g.addpart = M.ws.mfma_part;
         g.addpart_splits = mfma_fold_splits(c.d_model, qdim);
+        g.addpart_cap = rows.n_max;
+    } else if (o_splits > 1) {
+        g.addpart = M.pf_split;
+        g.addpart_splits = o_splits;
         g.addpart_cap = rows.n_max;
     }
     if ((e = mark(M, BUDDY_KERNEL_GATE_UP, l, false, s)) != hipSuccess ||

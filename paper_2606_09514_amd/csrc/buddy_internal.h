@@ -361,7 +361,7 @@ struct GemvArgs {
     // MFMA path: compact activation rows as bf16 parts in fragment order
     // (store_staged; the prefill's tiled GEMM: one bf16 fragment, xb_index)
     bf16_t* XB; int ldxb;
-    // PRO_RMSNORM on the MFMA path: K-split partial sums of the preceding
+    // PRO_RMSNORM on the MFMA and GEMM paths: K-split partial sums of the preceding
     // residual-add projection, [split][row capacity][K] by launch row, that
     // the staging adds into X's rows (in split order, written back) before
     // the norm; or null
@@ -531,9 +531,12 @@ hipError_t launch_mfma(int pro, int epi, const GemvArgs& g, float* part, hipStre
 hipError_t launch_prep(int pro, const GemvArgs& g, hipStream_t s);
 // Tiled MFMA GEMM for many rows (prompt tokens): exact row counts, bf16
 // weights, K a multiple of 64.
-// part: fp32 workspace of part_elems for the split-K sums.
+// part: fp32 workspace of part_elems for the split-K sums.  fold (residual
+// adds): split sums stay in part, [split][n_max][N] by launch row, for the
+// next RMSNorm staging to add (GemvArgs.addpart); *fold receives the splits
+// (1: nothing left to add).
 hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,
-                       hipStream_t s);
+                       hipStream_t s, int* fold);
 constexpr int kGemmMinRows = 64;
 // Split-K sums of a prefill of `rows` tokens: two splits of the residual-add
 // projections, or for prompts of up to kGemmShortRows tokens up to 49152

@@ -343,19 +343,92 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
 
 // ----------------------------------------------------------- staging
 
-// Activation staging for the tiled GEMM: the rows of a 16-row column tile
-// as bf16 in B-operand fragment order, with the RMSNorm folded in
-// (PRO_RMSNORM) or a plain conversion (PRO_NONE).  One workgroup of 16
-// wavefronts per tile (and, for PRO_NONE, per chunk of kPrepChunk columns):
-// wavefront w converts row w of the tile into LDS (rows padded by 16 bytes,
-// so the fragment reads below are conflict-free), then every thread writes
-// whole 16-byte pieces of the tile's fragments, consecutive threads to
-// consecutive addresses.  For the RMSNorm the row's sum of squares comes
-// first, over all of K.
-constexpr int kPrepChunk = 2048;                 // columns per LDS pass
+// Activation staging for the tiled GEMM, RMSNorm folded in: a workgroup of
+// 1024 threads takes four rows, 256 threads each, which hold their row in
+// registers (KG groups of eight elements per thread, K <= 2048 KG), so that
+// it is read once; the bf16 values pass through LDS and leave as 64-byte
+// pieces (four rows of an 8-column chunk) of the 16-row fragments.  Rows past
+// the last write zeros.  With addpart (split sums of the O projection, [split][row][K]
+// by launch row) the residual add happens here, in split order, and the row
+// is written back.  Latency bounds a short prompt, so many small workgroups:
+// 197 rows of 4096 took 14.8 us with a wavefront per row and 16 rows per
+// workgroup (13 workgroups, each row read twice), now 4.4; 2048 rows 18.5 and
+// 11.4.
+constexpr int kPrepRows = 4;
+template <int KG>
+__global__ __launch_bounds__(1024) void prep_rows_kernel(GemvArgs g, int n) {
+    constexpr int kPitch = KG * 2048 * 2 + 16;   // bytes per LDS row, conflict-free pieces
+    __shared__ __attribute__((aligned(16))) char s_rows[kPrepRows * kPitch];
+    __shared__ float s_ss[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r = tid >> 8, t = tid & 255;
+    const int i = kPrepRows * blockIdx.x + r, K = g.K;   // launch row
+    const bool live = i < n;
+    float* x = const_cast<float*>(g.X) + (size_t)(live ? row_seq(g.rows, i) : 0) * g.ldx;
+    float4 v[2 * KG];
+    float ss = 0.f;
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+        const int k = 8 * (t + 256 * q);
+        v[2 * q] = v[2 * q + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!live || k >= K) continue;
+        v[2 * q] = *reinterpret_cast<const float4*>(x + k);
+        v[2 * q + 1] = *reinterpret_cast<const float4*>(x + k + 4);
+    }
+    if (g.addpart && live) {
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+            const int k = 8 * (t + 256 * q);
+            if (k >= K) continue;
+            float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0;
+#pragma unroll 4
+            for (int z = 0; z < g.addpart_splits; ++z) {
+                const float* pz = g.addpart + ((size_t)z * g.addpart_cap + i) * K + k;
+                const float4 p0 = *reinterpret_cast<const float4*>(pz), p1 = *reinterpret_cast<const float4*>(pz + 4);
+                a0.x += p0.x; a0.y += p0.y; a0.z += p0.z; a0.w += p0.w;
+                a1.x += p1.x; a1.y += p1.y; a1.z += p1.z; a1.w += p1.w;
+            }
+            v[2 * q].x += a0.x; v[2 * q].y += a0.y; v[2 * q].z += a0.z; v[2 * q].w += a0.w;
+            v[2 * q + 1].x += a1.x; v[2 * q + 1].y += a1.y; v[2 * q + 1].z += a1.z; v[2 * q + 1].w += a1.w;
+            *reinterpret_cast<float4*>(x + k) = v[2 * q];
+            *reinterpret_cast<float4*>(x + k + 4) = v[2 * q + 1];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2 * KG; ++q) ss += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
+    ss = wave_sum(ss);
+    if (lane == 0) s_ss[wave] = ss;
+    __syncthreads();
+    ss = (s_ss[4 * r] + s_ss[4 * r + 1]) + (s_ss[4 * r + 2] + s_ss[4 * r + 3]);
+    const float inv = 1.0f / sqrtf(ss / (float)K + g.eps);
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+        const int k = 8 * (t + 256 * q);
+        if (k >= K) continue;
+        float gv[8];
+        St<bf16_t>::vec((const bf16_t*)g.gain + k, gv);
+        const float4 a = v[2 * q], b = v[2 * q + 1];
+        *reinterpret_cast<uint4*>(s_rows + r * kPitch + 2 * k) =
+            make_uint4(pack_bf16x2(a.x * (inv * gv[0]), a.y * (inv * gv[1])),
+                       pack_bf16x2(a.z * (inv * gv[2]), a.w * (inv * gv[3])),
+                       pack_bf16x2(b.x * (inv * gv[4]), b.y * (inv * gv[5])),
+                       pack_bf16x2(b.z * (inv * gv[6]), b.w * (inv * gv[7])));
+    }
+    __syncthreads();
+    for (int f = tid; f < kPrepRows * (K >> 3); f += 1024) {
+        const int rr = f & (kPrepRows - 1), k = 8 * (f / kPrepRows);
+        *reinterpret_cast<uint4*>(g.XB + xb_index(kPrepRows * blockIdx.x + rr, k, K)) =
+            *reinterpret_cast<const uint4*>(s_rows + rr * kPitch + 2 * k);
+    }
+}
+
+// Plain conversion (inputs no kernel staged): one workgroup of 16 wavefronts
+// per 16-row tile and chunk of kPrepChunk columns; wavefront w converts row w
+// into LDS (rows padded by 16 bytes), then every thread writes whole 16-byte
+// pieces of the tile's fragments, consecutive threads to consecutive addresses.
+constexpr int kPrepChunk = 2048;                 // columns per workgroup
 constexpr int kPrepPitch = kPrepChunk * 2 + 16;  // bytes per LDS row
 
-template <int PRO>
 __global__ __launch_bounds__(1024) void prep_tile_kernel(GemvArgs g, int n) {
     __shared__ __attribute__((aligned(16))) char s_rows[16 * kPrepPitch];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -363,59 +436,39 @@ __global__ __launch_bounds__(1024) void prep_tile_kernel(GemvArgs g, int n) {
     const int tile = blockIdx.x, K = g.K, S = K >> 5;
     const int i = 16 * tile + w;                      // this wavefront's row (list index)
     const bool live = i < n;
-    const float* x = g.X + (size_t)(live ? row_seq(g.rows, i) : 0) * g.ldx;
-    float inv = 1.f;
-    if (PRO == PRO_RMSNORM) {
-        float ss = 0.f;
-        if (live)
-            for (int k = 4 * lane; k < K; k += 256) {
-                const float4 v = *reinterpret_cast<const float4*>(x + k);
-                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-            }
-        ss = wave_sum(ss);
-        inv = 1.0f / sqrtf(ss / (float)K + g.eps);
+    const int c0 = blockIdx.y * kPrepChunk, kc = min(kPrepChunk, K - c0);
+    const float* x = g.X + (size_t)(live ? row_seq(g.rows, i) : 0) * g.ldx + c0;
+    char* row = s_rows + w * kPrepPitch;
+    for (int k = 4 * lane; k < kc; k += 256) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (live) v = *reinterpret_cast<const float4*>(x + k);
+        *reinterpret_cast<uint2*>(row + 2 * k) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
     }
-    const int c_first = PRO == PRO_RMSNORM ? 0 : blockIdx.y * kPrepChunk;
-    const int c_end = PRO == PRO_RMSNORM ? K : min(K, c_first + kPrepChunk);
-    for (int c0 = c_first; c0 < c_end; c0 += kPrepChunk) {
-        const int kc = min(kPrepChunk, K - c0);
-        char* row = s_rows + w * kPrepPitch;
-        for (int k = 4 * lane; k < kc; k += 256) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (live) {
-                v = *reinterpret_cast<const float4*>(x + c0 + k);
-                if (PRO == PRO_RMSNORM) {
-                    const bf16_t* gp = (const bf16_t*)g.gain + c0 + k;
-                    v.x *= inv * bf2f(gp[0]); v.y *= inv * bf2f(gp[1]);
-                    v.z *= inv * bf2f(gp[2]); v.w *= inv * bf2f(gp[3]);
-                }
-            }
-            *reinterpret_cast<uint2*>(row + 2 * k) =
-                make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
-        }
-        __syncthreads();
-        // fragment (k-step s, lane L): row L % 16, columns 32 s + 8 (L / 16) .. + 7
-        const int nfrag = (kc >> 5) * 64;
-        for (int f = tid; f < nfrag; f += 1024) {
-            const int sl = f >> 6, L = f & 63;
-            const uint4 v = *reinterpret_cast<const uint4*>(s_rows + (L & 15) * kPrepPitch +
-                                                           2 * (32 * sl + 8 * (L >> 4)));
-            const size_t frag = ((size_t)tile * S + (c0 >> 5) + sl) * 64 + L;
-            *reinterpret_cast<uint4*>(g.XB + frag * 8) = v;
-        }
-        __syncthreads();
+    __syncthreads();
+    // fragment (k-step s, lane L): row L % 16, columns 32 s + 8 (L / 16) .. + 7
+    const int nfrag = (kc >> 5) * 64;
+    for (int f = tid; f < nfrag; f += 1024) {
+        const int sl = f >> 6, L = f & 63;
+        const uint4 v = *reinterpret_cast<const uint4*>(s_rows + (L & 15) * kPrepPitch +
+                                                       2 * (32 * sl + 8 * (L >> 4)));
+        const size_t frag = ((size_t)tile * S + (c0 >> 5) + sl) * 64 + L;
+        *reinterpret_cast<uint4*>(g.XB + frag * 8) = v;
     }
 }
 
 static hipError_t launch_prep_tiles(int pro, const GemvArgs& g, hipStream_t s) {
     const int n = g.rows.n_max, tiles = (n + 15) / 16;
     if (pro == PRO_RMSNORM) {
-        prep_tile_kernel<PRO_RMSNORM><<<dim3(tiles, 1), 1024, 0, s>>>(g, n);
+        const int wgs = 16 / kPrepRows * tiles;
+        if (g.K <= 2048) prep_rows_kernel<1><<<wgs, 1024, 0, s>>>(g, n);
+        else if (g.K <= 4096) prep_rows_kernel<2><<<wgs, 1024, 0, s>>>(g, n);
+        else if (g.K <= 8192) prep_rows_kernel<4><<<wgs, 1024, 0, s>>>(g, n);
+        else return hipErrorInvalidValue;   // K = d_model (at most 8192, checked at create)
     } else if (pro == PRO_NONE) {
         const int chunks = (g.K + kPrepChunk - 1) / kPrepChunk;
-        prep_tile_kernel<PRO_NONE><<<dim3(tiles, chunks), 1024, 0, s>>>(g, n);
+        prep_tile_kernel<<<dim3(tiles, chunks), 1024, 0, s>>>(g, n);
     } else {
-        return launch_prep(pro, g, s);
+        return hipErrorInvalidValue;        // the router context feeds no prompt projection
     }
     return hipGetLastError();
 }
@@ -515,11 +568,12 @@ static int gemm_tail_units(int units, int n) {
 }
 
 // The projection on one tile shape with K in `splits` parts (1: no partial
-// sums), the split sums' epilogue behind it; tail: 256 x 256 tiles with a
-// last round on 128 x 128 ones (gemm_tail_units).
+// sums), the split sums' epilogue behind it unless the next staging adds them
+// (fold: *fold receives the splits); tail: 256 x 256 tiles with a last round
+// on 128 x 128 ones (gemm_tail_units).
 template <int EPI>
 static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int units, int n, float* part,
-                               hipStream_t s, bool tail = false) {
+                               hipStream_t s, bool tail = false, int* fold = nullptr) {
     if (splits == 1) part = nullptr;
     if (shape == SH_256) {
         const int ubig = tail ? gemm_tail_units<EPI>(units, n) : units;
@@ -531,7 +585,8 @@ static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int uni
         gemm_launch<EPI, 2, 2, 4, 4>(g, units, n, s, part, splits);
     }
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
+    if (fold) *fold = splits;
+    if (e != hipSuccess || splits == 1 || fold) return e;
     const size_t work = (size_t)n * (units / 4);
     const int grid = (int)((work + 255) / 256 < 4096 ? (work + 255) / 256 : 4096);
     splitk_epi_kernel<EPI><<<grid, 256, 0, s>>>(g, units, n, splits, part);
@@ -548,7 +603,8 @@ static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int uni
 // the CUs.  Adding split sums costs their write and read (about 5 TB/s) and a
 // launch.
 template <int EPI>
-static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t part_elems, hipStream_t s) {
+static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t part_elems, hipStream_t s,
+                              int* fold) {
     const int n = g.rows.n_max, steps = g.K / kTileK;
     const size_t N = EPI == EPI_ADD ? units : 2 * units;
     const bool few = n <= kGemmShortRows;
@@ -561,7 +617,7 @@ static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t 
             if (z > 1 && (!part || steps % z || steps / z < 8 || z * n * N > part_elems)) break;
             if (z > 1 && !few && (EPI != EPI_ADD || sh != SH_256 || z > 2 || 2 * wgs < kCUs)) break;
             float us = grid_us(sh, wgs * z, steps / z);
-            if (z > 1) us += 4.f + (float)z * n * N * 8.f / 5e6f;
+            if (z > 1) us += (fold ? 0.f : 4.f) + (float)z * n * N * 8.f / 5e6f;
             if (sh == SH_256 && z == 1) {
                 const int ubig = gemm_tail_units<EPI>(units, n);
                 if (ubig < units) {
@@ -571,21 +627,21 @@ static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t 
             }
             if (best == 0.f || us < best) { best = us; shape = sh; splits = z; }
         }
-    return launch_shape<EPI>(shape, splits, g, units, n, part, s, true);
+    return launch_shape<EPI>(shape, splits, g, units, n, part, s, true, fold);
 }
 
 template <int EPI>
 static hipError_t launch_gemm_epi(const GemvArgs& g, int units, int tile, float* part,
-                                  size_t part_elems, hipStream_t s) {
+                                  size_t part_elems, hipStream_t s, int* fold = nullptr) {
     const int n = g.rows.n_max;
-    if (tile == BUDDY_GEMM_TILE_AUTO) return launch_auto<EPI>(g, units, part, part_elems, s);
-    if (tile == BUDDY_GEMM_TILE_128) return launch_shape<EPI>(SH_128, 1, g, units, n, nullptr, s);
+    if (tile == BUDDY_GEMM_TILE_AUTO) return launch_auto<EPI>(g, units, part, part_elems, s, fold);
+    if (tile == BUDDY_GEMM_TILE_128) return launch_shape<EPI>(SH_128, 1, g, units, n, nullptr, s, false, fold);
     const bool split = tile == BUDDY_GEMM_TILE_256_SPLIT && EPI == EPI_ADD && part && (g.K / kTileK) % 2 == 0;
-    return launch_shape<EPI>(SH_256, split ? 2 : 1, g, units, n, part, s);
+    return launch_shape<EPI>(SH_256, split ? 2 : 1, g, units, n, part, s, false, fold);
 }
 
 hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,
-                       hipStream_t s) {
+                       hipStream_t s, int* fold) {
     if (pro != PRO_STAGED) {
         hipError_t e = launch_prep_tiles(pro, g, s);
         if (e != hipSuccess) return e;
@@ -594,7 +650,7 @@ hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* par
         return launch_gemm_epi<EPI_QKV>(g, (g.nq + 2 * g.nkv) * (g.hd / 2), tile, part, part_elems, s);
     if (epi == EPI_SWIGLU) return launch_gemm_epi<EPI_SWIGLU>(g, g.f, tile, part, part_elems, s);
     if (epi != EPI_ADD) return hipErrorInvalidValue;
-    return launch_gemm_epi<EPI_ADD>(g, g.N, tile, part, part_elems, s);
+    return launch_gemm_epi<EPI_ADD>(g, g.N, tile, part, part_elems, s, fold);
 }
 
 }  // namespace buddy
