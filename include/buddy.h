@@ -351,15 +351,15 @@ buddy_status buddy_set_launch_policy(buddy_model* m, int32_t policy);
 /* Output tile of the prefill's tiled projections (bf16 weights, many prompt
  * tokens).
  *   BUDDY_GEMM_TILE_AUTO (default): the tile (128 x 128, 128 x 256 or
- *     256 x 256, the last with a final, partly filled round on 128 x 128
+ *     256 x 256, the last with a final, partly filled round on 128 x 256
  *     ones) and K split of least estimated time for the projection's weight
  *     rows and prompt tokens.  Up to 1536 tokens any projection may split K
  *     in up to eight parts; beyond, the residual-add projections (O, down)
  *     in two.  The parts' sums are added in a fixed order;
  *   BUDDY_GEMM_TILE_128, BUDDY_GEMM_TILE_256: always that tile (weight
  *     rows x token rows), K never split;
- *   BUDDY_GEMM_TILE_256_SPLIT: 256 x 256, K split for the residual-add
- *     projections.
+ *   BUDDY_GEMM_TILE_256_SPLIT: 256 x 256, K split in two for the
+ *     residual-add projections (where K is a multiple of 128).
  * The tiles without a split give the same results bit for bit; a split
  * adds the two half sums, a different rounding order. */
 typedef enum {

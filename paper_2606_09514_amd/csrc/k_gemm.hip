@@ -17,10 +17,12 @@
 // With eight wavefronts the two of each SIMD run in antiphase (below).  What
 // bounds the 256 x 256 tile is the MFMA and what does not overlap it: gate/up
 // of a 2048-token prompt (Llama-8B shape, three rounds of tiles) 357 us with
-// the wavefronts in phase, 328 to 338 in antiphase, 1.1 PFLOP/s where a
-// large library product of random bf16 values reaches 1.46 on this card.
+// the wavefronts in phase, 328 to 338 in antiphase, 321 with the weights in
+// whole lines as well: 1.28 PFLOP/s, where a large library product of random
+// bf16 values reaches 1.46 on this card.
 // Both operands pass through LDS in MFMA fragment order, so each wavefront
-// reads a fragment as one conflict-free 16-byte read per lane:
+// reads a fragment as one conflict-free 16-byte read per lane (the weights of
+// the eight-wavefront tiles lie in whole lines instead, see the loads):
 //   A fragment (row tile rt): 1 KB at rt KB of the step's buffer, lane
 //     i + 16 q holding tile row 16 rt + i, k = 8 q .. + 7 of the step;
 //   B fragment (column tile ct): 1 KB after the A fragments, copied as is
@@ -45,6 +47,7 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 constexpr int kTileK = 32;
 constexpr int kFragBytes = 1024;                 // one 16 x 32 bf16 fragment
 constexpr int kBufs = 4;                         // K steps in LDS, three ahead
+constexpr int kPairBufs = 3;                     // pairs of K steps of weights in LDS
 
 // s_waitcnt operand: at most n vector-memory operations outstanding, other
 // counters unconstrained (gfx9 encoding: vmcnt low bits 3:0 and high bits
@@ -133,15 +136,19 @@ __device__ __forceinline__ void mfma_rows(f32x4_t (&acc)[TI][TJ], u32x4_t* a, u3
 template <int WM, int WN, int TI, int TJ>
 struct GemmShape {
     static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
-    // eight wavefronts, two per SIMD, one workgroup per CU
-    static constexpr bool kPingPong = kWaves == 8;
     static constexpr int kRowTiles = WM * TI, kColTiles = WN * TJ;
     static constexpr int kRows = 16 * kRowTiles, kCols = 16 * kColTiles;
+    // eight wavefronts: antiphase, weights in whole cache lines (pairs of K
+    // steps in three buffers), one workgroup per CU
+    static constexpr bool kPingPong = kWaves == 8;
+    static constexpr int kPairBytes = kRowTiles * 2 * kFragBytes;
     static constexpr int kBufBytes = (kRowTiles + kColTiles) * kFragBytes;
+    static constexpr int kLds = kPingPong ? kPairBufs * kPairBytes + kBufs * kColTiles * kFragBytes
+                                          : kBufs * kBufBytes;
     // fragments each wavefront loads per K step
     static constexpr int kALoads = kRowTiles / kWaves, kBLoads = kColTiles / kWaves;
     static_assert(kRowTiles % kWaves == 0 && kColTiles % kWaves == 0, "even load split");
-    static_assert(kBufs * kBufBytes <= 128 * 1024, "LDS");
+    static_assert(kLds <= 160 * 1024, "LDS");
     static_assert(TJ == 4 && (TI == 4 || TI == 8), "wavefront tile");
 };
 
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2,
 void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
     using Sh = GemmShape<WM, WN, TI, TJ>;
     constexpr bool kPaired = EPI == EPI_SWIGLU || EPI == EPI_QKV;
-    __shared__ __attribute__((aligned(16))) char s_buf[kBufs * Sh::kBufBytes];
+    __shared__ __attribute__((aligned(128))) char s_buf[Sh::kLds];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -179,44 +186,69 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
     // Direct global -> LDS loads (each lane's 16 bytes land at the wave's LDS
     // base + 16 lane): wavefront w loads row tiles kALoads w .. and column
     // tiles kBLoads w .. of every step.
-    // A fragment lane i + 16 q: tile row 16 rt + i, k = 8 q of the step.
-    const bf16_t* arow[Sh::kALoads];
-#pragma unroll
-    for (int t = 0; t < Sh::kALoads; ++t) {
-        const int r = 16 * (Sh::kALoads * wave + t) + (lane & 15);
-        int row;
-        if (kPaired) {
+    constexpr bool PP = Sh::kPingPong;
+    constexpr int kARows = PP ? 2 : 1;        // loads (row addresses) per row tile
+    auto weight_row = [&](int r) {            // row r of the tile
+        if constexpr (kPaired) {
             const int half = Sh::kRows / 2;
             const int u = min(u0 + (r % half), units - 1);
             int r0, r1;
             unit_rows<EPI>(g, u, r0, r1);
-            row = r < half ? r0 : r1;
+            return r < half ? r0 : r1;
         } else {
-            row = min(u0 + r, units - 1);
+            return min(u0 + r, units - 1);
         }
-        arow[t] = (const bf16_t*)g.W + (size_t)row * K + 8 * (lane >> 4);
-    }
+    };
+    // A, one step per load: fragment lane i + 16 q holds tile row 16 rt + i,
+    // k = 8 q of the step.  PP, two steps per pair of loads: load h of a row
+    // tile brings rows 8 h .. 8 h + 7, one whole 128-byte line each (two steps of
+    // 32; half lines cost the memory system as many requests as whole ones),
+    // lane L's chunk L % 8 of row L / 8 holding source chunk (L % 8) ^ (row % 8),
+    // which spreads the fragment reads over the banks.
+    const bf16_t* arow[Sh::kALoads][kARows];
+#pragma unroll
+    for (int t = 0; t < Sh::kALoads; ++t)
+#pragma unroll
+        for (int h = 0; h < kARows; ++h) {
+            const int rl = PP ? 8 * h + (lane >> 3) : lane & 15;
+            const int chunk = PP ? (lane & 7) ^ (lane >> 3) : lane >> 4;
+            arow[t][h] = (const bf16_t*)g.W + (size_t)weight_row(16 * (Sh::kALoads * wave + t) + rl) * K + 8 * chunk;
+        }
     const bf16_t* bfrag[Sh::kBLoads];
 #pragma unroll
     for (int t = 0; t < Sh::kBLoads; ++t) {
         const int c = min((t0 >> 4) + Sh::kBLoads * wave + t, last_tile);   // repeats of the last tile are discarded
         bfrag[t] = g.XB + ((size_t)c * S * 64 + lane) * 8;
     }
-    // one load per fragment; steps past the end reload the last one into a
-    // buffer that is not read again
-    auto issue = [&](int kb) {
+    constexpr int kBBase = PP ? kPairBufs * Sh::kPairBytes : Sh::kRowTiles * kFragBytes;
+    constexpr int kBStep = PP ? Sh::kColTiles * kFragBytes : Sh::kBufBytes;
+    // steps (pairs) past the end reload the last one into a buffer that is not
+    // read again
+    auto issue_b = [&](int kb) {
         const int kc = k0 + min(kb, nk - 1);
-        char* base = s_buf + (kb % kBufs) * Sh::kBufBytes;
-#pragma unroll
-        for (int t = 0; t < Sh::kALoads; ++t)
-            __builtin_amdgcn_global_load_lds((gptr_t)(arow[t] + kc * kTileK),
-                                             (lptr_t)(base + (Sh::kALoads * wave + t) * kFragBytes),
-                                             16, 0, 0);
 #pragma unroll
         for (int t = 0; t < Sh::kBLoads; ++t)
             __builtin_amdgcn_global_load_lds(
                 (gptr_t)(bfrag[t] + (size_t)kc * 512),
-                (lptr_t)(base + (Sh::kRowTiles + Sh::kBLoads * wave + t) * kFragBytes), 16, 0, 0);
+                (lptr_t)(s_buf + kBBase + (kb % kBufs) * kBStep + (Sh::kBLoads * wave + t) * kFragBytes), 16, 0, 0);
+    };
+    auto issue_a = [&](int kb) {   // one step's fragments (128 x 128 tile)
+        const int kc = k0 + min(kb, nk - 1);
+#pragma unroll
+        for (int t = 0; t < Sh::kALoads; ++t)
+            __builtin_amdgcn_global_load_lds((gptr_t)(arow[t][0] + kc * kTileK),
+                                             (lptr_t)(s_buf + (kb % kBufs) * Sh::kBufBytes +
+                                                      (Sh::kALoads * wave + t) * kFragBytes),
+                                             16, 0, 0);
+    };
+    auto issue_half = [&](int pair, int pbuf, int h) {   // rows 8 h .. of a pair of steps
+        const int kc = k0 + 2 * min(pair, nk / 2 - 1);
+#pragma unroll
+        for (int t = 0; t < Sh::kALoads; ++t)
+            __builtin_amdgcn_global_load_lds((gptr_t)((h ? arow[t][kARows - 1] : arow[t][0]) + kc * kTileK),
+                                             (lptr_t)(s_buf + pbuf * Sh::kPairBytes +
+                                                      (Sh::kALoads * wave + t) * 2 * kFragBytes + h * kFragBytes),
+                                             16, 0, 0);
     };
     constexpr int kLoads = Sh::kALoads + Sh::kBLoads;   // per wavefront and step
 
@@ -230,24 +262,22 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
     // TI/2 tiles of the lower half); otherwise TI tiles from wm TI.  Column
     // tiles: TJ from wn TJ.
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)s_buf;
-    const uint32_t a_off = lds0 + lane * 16 + (kPaired ? wm * TI / 2 : wm * TI) * kFragBytes;
-    const uint32_t b_off = lds0 + lane * 16 + (Sh::kRowTiles + wn * TJ) * kFragBytes;
+    const uint32_t b_off = lds0 + lane * 16 + kBBase + wn * TJ * kFragBytes;
+    constexpr int F = PP ? 2 * kFragBytes : kFragBytes;                 // a row tile's bytes
+    // PP: row i = lane % 16 of a tile, chunk 4 u + lane / 16 of step u of the
+    // pair, at that chunk ^ (i % 8): bit 6 of the address flips with u
+    const uint32_t a_off = lds0 + (PP ? (lane & 15) * 128 + (((lane >> 4) ^ (lane & 7)) * 16) : lane * 16) +
+                           (kPaired ? wm * TI / 2 : wm * TI) * F;
     constexpr int kSecond = kPaired ? Sh::kRowTiles / 2 - TI / 2 : 0;   // gap to the second rows
-    constexpr int F = kFragBytes;
 
-    auto read_frags = [&](int kb, u32x4_t* a, u32x4_t* bv) {
-        const uint32_t sb = (kb % kBufs) * Sh::kBufBytes;
+    auto read_frags = [&](uint32_t aa, uint32_t bb, u32x4_t* a, u32x4_t* bv) {
         if constexpr (TI == 4) {
-            lds_issue8<0, F, (2 + kSecond) * F, (3 + kSecond) * F>(a_off + sb, b_off + sb, a, bv);
+            lds_issue8<0, F, (2 + kSecond) * F, (3 + kSecond) * F>(aa, bb, a, bv);
         } else {
-            lds_issue8<0, F, 2 * F, 3 * F>(a_off + sb, b_off + sb, a, bv);
-            lds_issue4<(4 + kSecond) * F, (5 + kSecond) * F, (6 + kSecond) * F, (7 + kSecond) * F>(
-                a_off + sb, a + 4);
+            lds_issue8<0, F, 2 * F, 3 * F>(aa, bb, a, bv);
+            lds_issue4<(4 + kSecond) * F, (5 + kSecond) * F, (6 + kSecond) * F, (7 + kSecond) * F>(aa, a + 4);
         }
     };
-    issue(0);
-    issue(1);
-    issue(2);
     if constexpr (Sh::kPingPong) {
         // Two wavefronts per SIMD in antiphase: while wavefronts 0 .. 3 (one
         // per SIMD) multiply a step from registers, wavefronts 4 .. 7 read
@@ -262,14 +292,31 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
         // Step k's buffer is refilled with step k + 4's loads by the reads of
         // step k + 1 (phase 2 k + 2 at the earliest): everyone has read step k
         // by the end of phase 2 k + 1, its reads waited for before the barrier.
+        // The weights of a pair of steps P arrive in halves, issued while
+        // reading steps 2 P - 4 and 2 P - 3, each with the B tiles of the step
+        // three ahead: the counts above hold for both, and a pair's buffer (P % 3)
+        // held pair P - 3, whose steps everyone has read by then.
         const bool late = wave >= 4;
+        issue_half(0, 0, 0);
+        issue_half(0, 0, 1);
+        issue_b(0);
+        issue_half(1, 1, 0);
+        issue_b(1);
+        issue_half(1, 1, 1);
+        issue_b(2);
         __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
         asm volatile("s_barrier" ::: "memory");
         if (late) asm volatile("s_barrier" ::: "memory");   // phase 0 is the early wavefronts'
+        int pread = 0, pload = 2;                            // pair buffers of this step's reads and loads
         for (int kb = 0; kb < nk; ++kb) {
             u32x4_t a[TI], bv[TJ];
-            read_frags(kb, a, bv);
-            issue(kb + 3);
+            read_frags((a_off + pread * Sh::kPairBytes) ^ ((kb & 1) * 64), b_off + (kb % kBufs) * kBStep, a, bv);
+            issue_half((kb >> 1) + 2, pload, kb & 1);
+            issue_b(kb + 3);
+            if (kb & 1) {
+                pread = pread == kPairBufs - 1 ? 0 : pread + 1;
+                pload = pload == kPairBufs - 1 ? 0 : pload + 1;
+            }
             lds_wait_all<TI>(a, bv);
             if (late) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
             __builtin_amdgcn_sched_barrier(0);
@@ -295,14 +342,20 @@ void gemm_kernel(GemvArgs g, int units, int n, float* part, int ubase) {
         // outstanding, barrier (every wavefront's loads of step kb have landed
         // and every wavefront has read step kb - 1's buffer), refill that
         // buffer with step kb + 3, multiply step kb.
+        for (int kb = 0; kb < 3; ++kb) {
+            issue_a(kb);
+            issue_b(kb);
+        }
         for (int kb = 0; kb < nk; ++kb) {
             __builtin_amdgcn_s_waitcnt(vmcnt_at_most(2 * kLoads));
             // a plain barrier: __syncthreads() would also wait for every load
             // in flight (its fence covers the direct-to-LDS writes)
             asm volatile("s_barrier" ::: "memory");
-            issue(kb + 3);
+            issue_a(kb + 3);
+            issue_b(kb + 3);
             u32x4_t a[TI], bv[TJ];
-            read_frags(kb, a, bv);
+            const uint32_t sb = (kb % kBufs) * Sh::kBufBytes;
+            read_frags(a_off + sb, b_off + sb, a, bv);
             mfma_rows<0>(acc, a, bv);
         }
     }
@@ -543,34 +596,33 @@ static dim3 shape_grid(int shape, int units, int n) {
 static float grid_us(int shape, int wgs, int steps) {
     if (shape == SH_128) {
         const int rest = wgs % (2 * kCUs);
-        return steps * (0.69f * (wgs / (2 * kCUs)) + (rest > kCUs ? 0.69f : rest > 0 ? 0.33f : 0.f));
+        return steps * (0.74f * (wgs / (2 * kCUs)) + (rest > kCUs ? 0.74f : rest > 0 ? 0.36f : 0.f));
     }
-    return steps * (shape == SH_256 ? 0.8f : 0.47f) * ((wgs + kCUs - 1) / kCUs);
+    return steps * (shape == SH_256 ? 0.84f : 0.57f) * ((wgs + kCUs - 1) / kCUs);
 }
 
 // The last round of a 256 x 256 grid that does not fill the CUs: the units
 // of the row tiles that fill whole rounds stay on 256 x 256 tiles, and the
-// rest go to a second launch of 128 x 128 tiles when those take one round
-// of two workgroups per CU (half the flops of a large round, at about 0.8
-// of the large tile's rate per flop measured on the MI355X: some 0.6 of its
-// time) instead of a partly idle round of the large one.  Returns the
-// first unit of the 128 x 128 launch, or units for none.  The outputs are
-// the same bit for bit: every output sums its K steps in the same order in
-// either tile.
+// rest go to a second launch of 128 x 256 tiles when those take one round
+// (0.57 of a large round's 0.84 us a step) instead of a partly idle round of
+// the large one (gate/up of a 2048-token prompt, Llama-8B shape, half a round
+// left: 95 us on 128 x 128 tiles, two to a CU, now 66).  Returns the first
+// unit of the second launch, or units for none.  The outputs are the same bit
+// for bit: every output sums its K steps in the same order in either tile.
 template <int EPI>
 static int gemm_tail_units(int units, int n) {
-    const dim3 big = gemm_grid<EPI, 2, 4, 8, 4>(units, n);
+    const dim3 big = shape_grid<EPI>(SH_256, units, n);
     const int tiles = big.x * big.y, whole = tiles / kCUs * kCUs;
     if (whole == tiles || whole == 0) return units;
     const int ubig = whole / big.y * tile_units<EPI, 2, 4, 8, 4>();
-    const dim3 small = gemm_grid<EPI, 2, 2, 4, 4>(units - ubig, n);
-    return small.x * small.y <= 2 * kCUs ? ubig : units;
+    const dim3 rest = shape_grid<EPI>(SH_128x256, units - ubig, n);
+    return (int)(rest.x * rest.y) <= kCUs ? ubig : units;
 }
 
 // The projection on one tile shape with K in `splits` parts (1: no partial
 // sums), the split sums' epilogue behind it unless the next staging adds them
 // (fold: *fold receives the splits); tail: 256 x 256 tiles with a last round
-// on 128 x 128 ones (gemm_tail_units).
+// on 128 x 256 ones (gemm_tail_units).
 template <int EPI>
 static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int units, int n, float* part,
                                hipStream_t s, bool tail = false, int* fold = nullptr) {
@@ -578,7 +630,7 @@ static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int uni
     if (shape == SH_256) {
         const int ubig = tail ? gemm_tail_units<EPI>(units, n) : units;
         gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s, part, splits, 0, ubig);
-        if (ubig < units) gemm_launch<EPI, 2, 2, 4, 4>(g, units, n, s, nullptr, 1, ubig);
+        if (ubig < units) gemm_launch<EPI, 2, 4, 4, 4>(g, units, n, s, nullptr, 1, ubig);
     } else if (shape == SH_128x256) {
         gemm_launch<EPI, 2, 4, 4, 4>(g, units, n, s, part, splits);
     } else {
@@ -614,16 +666,14 @@ static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t 
         for (int z = 1; z <= 8; z *= 2) {
             const dim3 grid = shape_grid<EPI>(sh, units, n);
             const int wgs = grid.x * grid.y;
-            if (z > 1 && (!part || steps % z || steps / z < 8 || z * n * N > part_elems)) break;
+            // whole pairs of steps; K is a multiple of 64
+            if (z > 1 && (!part || steps % (2 * z) || steps / z < 8 || z * n * N > part_elems)) break;
             if (z > 1 && !few && (EPI != EPI_ADD || sh != SH_256 || z > 2 || 2 * wgs < kCUs)) break;
             float us = grid_us(sh, wgs * z, steps / z);
             if (z > 1) us += (fold ? 0.f : 4.f) + (float)z * n * N * 8.f / 5e6f;
             if (sh == SH_256 && z == 1) {
                 const int ubig = gemm_tail_units<EPI>(units, n);
-                if (ubig < units) {
-                    const dim3 small = gemm_grid<EPI, 2, 2, 4, 4>(units - ubig, n);
-                    us = grid_us(sh, wgs / kCUs * kCUs, steps) + grid_us(SH_128, small.x * small.y, steps);
-                }
+                if (ubig < units) us = grid_us(sh, wgs / kCUs * kCUs, steps) + grid_us(SH_128x256, 1, steps);
             }
             if (best == 0.f || us < best) { best = us; shape = sh; splits = z; }
         }
@@ -636,7 +686,7 @@ static hipError_t launch_gemm_epi(const GemvArgs& g, int units, int tile, float*
     const int n = g.rows.n_max;
     if (tile == BUDDY_GEMM_TILE_AUTO) return launch_auto<EPI>(g, units, part, part_elems, s, fold);
     if (tile == BUDDY_GEMM_TILE_128) return launch_shape<EPI>(SH_128, 1, g, units, n, nullptr, s, false, fold);
-    const bool split = tile == BUDDY_GEMM_TILE_256_SPLIT && EPI == EPI_ADD && part && (g.K / kTileK) % 2 == 0;
+    const bool split = tile == BUDDY_GEMM_TILE_256_SPLIT && EPI == EPI_ADD && part && (g.K / kTileK) % 4 == 0;
     return launch_shape<EPI>(SH_256, split ? 2 : 1, g, units, n, part, s, false, fold);
 }
 
