@@ -715,6 +715,7 @@ void attn_prefill_kernel(AttnArgs a) {
     const int qt = qr / G, hq = qr - qt * G;
     const bool q_ok = qt < count;
     const int q_pos = pos0 + qt;
+    const int pos_first = pos0 + 16 * wave / G;        // of the wavefront's query rows
     bf16x8_t qh[4], ql[4];
     {
         const int bq = row_seq(a.rows, first + min(qt, count - 1));
@@ -825,20 +826,27 @@ void attn_prefill_kernel(AttnArgs a) {
             }
             st[t] = d;
         }
-        // causal mask and online softmax of query row lane % 16
-        const int r0 = kt * kPfRows + 4 * lg;
+        // causal mask and online softmax of query row lane % 16.  Only tiles
+        // that reach past the wavefront's first position hold masked rows
+        // (query rows past the group's are computed and never written).  The
+        // exponentials are single v_exp_f32: weights below 2^-126 are 0, which
+        // no row's sum of at least 1 can hold.
+        if (kt * kPfRows + kPfRows - 1 > pos_first) {
+            const int r0 = kt * kPfRows + 4 * lg;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    st[t][e] = r0 + 16 * t + e <= q_pos ? st[t][e] : -INFINITY;
+        }
         float mx = -INFINITY;
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = r0 + 16 * t + e;
-                st[t][e] = q_ok && row <= q_pos ? st[t][e] : -INFINITY;
-                mx = fmaxf(mx, st[t][e]);
-            }
+            mx = fmaxf(mx, fmaxf(fmaxf(st[t][0], st[t][1]), fmaxf(st[t][2], st[t][3])));
         mx = max_xor32(max_xor16(mx));
         const float mn = fmaxf(m_run, mx);
-        const float al = scale_of(m_run, mn);
+        const float ms = mn == -INFINITY ? 0.f : mn;   // every row masked: weights exp2(-inf) = 0
+        const float al = __builtin_amdgcn_exp2f(m_run - ms);
         float ls = 0.f;
         s16x4_t pa[4];
 #pragma unroll
@@ -846,7 +854,7 @@ void attn_prefill_kernel(AttnArgs a) {
             float p[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                p[e] = scale_of(st[t][e], mn);
+                p[e] = __builtin_amdgcn_exp2f(st[t][e] - ms);
                 ls += p[e];
             }
             pa[t] = __builtin_bit_cast(s16x4_t, make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3])));
@@ -854,14 +862,17 @@ void attn_prefill_kernel(AttnArgs a) {
         ls = sum_xor32(sum_xor16(ls));
         l_run = l_run * al + ls;
         m_run = mn;
-        // rescale O: lane d + 16 r holds query rows 4 r .. 4 r + 3
-        float ar[4];
+        // rescale O (lane d + 16 r holds query rows 4 r .. 4 r + 3) unless no
+        // row's running max moved; a multiply by 1 would change nothing
+        if (__any(al != 1.f)) {
+            float ar[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ar[e] = __shfl(al, 4 * lg + e, kWave);
+            for (int e = 0; e < 4; ++e) ar[e] = __shfl(al, 4 * lg + e, kWave);
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt)
+            for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[dt][e] *= ar[e];
+                for (int e = 0; e < 4; ++e) o[dt][e] *= ar[e];
+        }
         // O += P V, 16 rows at a time
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
