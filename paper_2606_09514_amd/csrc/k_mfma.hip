@@ -284,11 +284,17 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         for (int c = 0; c < NT; ++c)
             Bp[c] = g.XB + (((size_t)((j0 >> 4) + min(c, nct - 1)) * S + kw) * (64 * FR) + lane) * 8;
 
-        f32x4_t acc[RT][NT];
+        // PACK: even and odd k-steps accumulate apart (shorter chains of fp32
+        // additions: the GEMV that small batches took before sums 64 lanes'
+        // short chains as a tree)
+        constexpr int NA = PACK ? 2 : 1;
+        f32x4_t acc[RT][NT], odd[PACK ? RT : 1];
 #pragma unroll
-        for (int t = 0; t < RT; ++t)
+        for (int t = 0; t < RT; ++t) {
 #pragma unroll
             for (int c = 0; c < NT; ++c) acc[t][c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            if (PACK) odd[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        }
 
         if (j0 > 0) __syncthreads();   // the previous group's epilogue is done with the LDS
         issue_a(0, 0);
@@ -356,10 +362,16 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
 #pragma unroll
-                        for (int c = 0; c < NT; ++c)
-                            acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        for (int c = 0; c < NT; ++c) {
+                            f32x4_t& to = u % NA ? odd[PACK ? t : 0] : acc[t][c];
+                            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 __builtin_bit_cast(bf16x8_t, a[t][u]),
-                                __builtin_bit_cast(bf16x8_t, bv[u][p][c]), acc[t][c], 0, 0, 0);
+                                __builtin_bit_cast(bf16x8_t, bv[u][p][c]), to, 0, 0, 0);
+                        }
+        }
+        if constexpr (PACK) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t][0] += odd[t];
         }
 
         // per epilogue group: reduce the four K-slices through LDS, then the
