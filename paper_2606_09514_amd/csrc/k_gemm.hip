@@ -621,14 +621,15 @@ static int gemm_tail_units(int units, int n) {
 
 // The projection on one tile shape with K in `splits` parts (1: no partial
 // sums), the split sums' epilogue behind it unless the next staging adds them
-// (fold: *fold receives the splits); tail: 256 x 256 tiles with a last round
-// on 128 x 256 ones (gemm_tail_units).
+// (fold: *fold receives the splits); tail: unsplit 256 x 256 tiles with a last
+// round on 128 x 256 ones (gemm_tail_units).
 template <int EPI>
 static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int units, int n, float* part,
                                hipStream_t s, bool tail = false, int* fold = nullptr) {
     if (splits == 1) part = nullptr;
     if (shape == SH_256) {
-        const int ubig = tail ? gemm_tail_units<EPI>(units, n) : units;
+        // never with a K split: the split sums added behind are those of every unit
+        const int ubig = tail && splits == 1 ? gemm_tail_units<EPI>(units, n) : units;
         gemm_launch<EPI, 2, 4, 8, 4>(g, units, n, s, part, splits, 0, ubig);
         if (ubig < units) gemm_launch<EPI, 2, 4, 4, 4>(g, units, n, s, nullptr, 1, ubig);
     } else if (shape == SH_128x256) {

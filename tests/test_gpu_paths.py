@@ -139,3 +139,34 @@ def test_prefill_short_prompts(lens):
     for b, n in enumerate(lens):
         a, p = auto[0][b, :n], plain[0][b, :n]
         assert np.max(np.abs(a - p)) <= 1e-2 * np.max(np.abs(p))
+
+
+def test_prefill_split_and_tail_columns():
+    """A down projection of 257 to 384 tiles of 256 x 256 (16 x 17 here) over a deep K: the
+    automatic choice splits K, and the tile's last, partly filled round must then stay with the
+    first launch, for the split sums of every weight row are added behind it.  An earlier prefill of
+    the handle, split without a tail, has left its sums in the partial buffer.  Every hidden column
+    against the unsplit 128 x 128 tile: the sums differ in their order only, and what the next
+    projections read is rounded to bf16 (2^-9 a value): 1e-2 of a column's norm is allowed, sums
+    added twice or out of an older call are of the column's own size."""
+    n = 4100
+    shape = dict(n_layers=3, d_model=4096, n_heads=8, n_kv_heads=2, head_dim=128, d_ffn=14336,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    cfg = synth.model_config(shape, "bf16", n)
+    model = blib.Model(cfg, synth.model_weights(cfg, 250, "cuda", omega=0.1), max_batch=1)
+    k, v = synth.kv_cache(cfg, 1, 0, 251, "cuda")
+    gen = torch.Generator(device="cuda").manual_seed(252)
+    x, other = (torch.randn((1, n, 4096), generator=gen, device="cuda") for _ in range(2))
+
+    def prefill(inp, tile):
+        model.set_gemm_tile(tile)
+        hidden = inp.clone()
+        model.prefill(k, v, hidden, [n], [1])
+        return hidden[0].double()
+
+    plain = prefill(x, blib.GEMM_TILE_128)
+    for tile in (blib.GEMM_TILE_AUTO, blib.GEMM_TILE_256_SPLIT):
+        prefill(other, blib.GEMM_TILE_256_SPLIT)
+        err = (prefill(x, tile) - plain).norm(dim=0) / plain.norm(dim=0)
+        print(tile, float(err.max()), flush=True)
+        assert float(err.max()) < 1e-2, (tile, int(err.argmax()))
