@@ -168,8 +168,8 @@ hipError_t launch_proj(const Model& M, int batch, int pro, int epi, GemvArgs g, 
                        bool fold = false, float* fold_part = nullptr, int* gemm_fold = nullptr) {
     // prompt tokens of a prefill: the tiled GEMM
     if (uses_gemm(M, g.rows, batch, g.K, g.tok_T))
-        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, M.pf_rows), s,
-                           gemm_fold);
+        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, g.rows.n_max),
+                           s, gemm_fold);
     if (uses_mfma(M, g.rows, batch, g.K, g.tok_T))
         return launch_mfma(pro, epi, g,
                            fold_part ? fold_part

@@ -540,7 +540,10 @@ hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* par
 constexpr int kGemmMinRows = 64;
 // Split-K sums of a prefill of `rows` tokens: two splits of the residual-add
 // projections, or for prompts of up to kGemmShortRows tokens up to 49152
-// (splits x weight rows) per token, 128 MB at most.
+// (splits x weight rows) per token, 128 MB at most.  It grows with rows: a
+// launch is allowed what a buffer for its own rows would hold, whatever larger
+// prompt the handle's buffer was allocated for, so that the K splits, and with
+// them the order of the sums, do not depend on earlier calls.
 constexpr int kGemmShortRows = 1536;
 inline size_t gemm_part_elems(const buddy_config& c, size_t rows) {
     const size_t two = 2 * rows * c.d_model;

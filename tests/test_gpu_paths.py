@@ -170,3 +170,26 @@ def test_prefill_split_and_tail_columns():
         err = (prefill(x, tile) - plain).norm(dim=0) / plain.norm(dim=0)
         print(tile, float(err.max()), flush=True)
         assert float(err.max()) < 1e-2, (tile, int(err.argmax()))
+
+
+def test_prefill_same_bits_after_a_longer_prompt():
+    """The K splits of a prompt's projections follow from its own tokens: the partial buffer that
+    an earlier, longer prompt left on the handle must not allow more of them (gate/up of 150
+    tokens at this width would be split in two there, which its own buffer has no room for)."""
+    n, long = 150, 1100
+    shape = dict(n_layers=3, d_model=4096, n_heads=8, n_kv_heads=2, head_dim=128, d_ffn=14336,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    cfg = synth.model_config(shape, "bf16", long)
+    model = blib.Model(cfg, synth.model_weights(cfg, 260, "cuda", omega=0.1), max_batch=1)
+    k, v = synth.kv_cache(cfg, 1, 0, 261, "cuda")
+    gen = torch.Generator(device="cuda").manual_seed(262)
+    x, other = (torch.randn((1, t, 4096), generator=gen, device="cuda") for t in (n, long))
+
+    def prefill(inp):
+        hidden = inp.clone()
+        model.prefill(k, v, hidden, [inp.shape[1]], [1])
+        return [hidden] + [c[:, :, :, :n].clone() for c in (k, v)]
+
+    fresh = prefill(x)
+    prefill(other)
+    assert all(torch.equal(a, b) for a, b in zip(fresh, prefill(x)))
