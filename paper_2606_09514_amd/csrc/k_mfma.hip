@@ -347,8 +347,9 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                 }
             }
             // a half round's second k-step multiplies zeros (adds exactly 0):
-            // the MFMAs stay unconditional
-            if constexpr (KR == 2) {
+            // the MFMAs stay unconditional.  PACK leaves it out instead: the
+            // weights there are copies, and an infinite one times 0 is NaN
+            if constexpr (KR == 2 && !PACK) {
                 const uint32_t keep = half ? 0u : ~0u;
 #pragma unroll
                 for (int c = 0; c < NT; ++c)
@@ -356,7 +357,8 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                     for (int p = 0; p < FR; ++p) bv[1][p][c] &= keep;
             }
 #pragma unroll
-            for (int u = 0; u < KR; ++u)
+            for (int u = 0; u < KR; ++u) {
+                if (PACK && KR == 2 && u == 1 && half) break;
 #pragma unroll
                 for (int p = 0; p < FR; ++p)
 #pragma unroll
@@ -368,6 +370,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                                 __builtin_bit_cast(bf16x8_t, a[t][u]),
                                 __builtin_bit_cast(bf16x8_t, bv[u][p][c]), to, 0, 0, 0);
                         }
+            }
         }
         if constexpr (PACK) {
 #pragma unroll
@@ -380,12 +383,15 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         auto sum4 = [&](int t, int il, int c) {
             return (s_red[0][t][il][c] + s_red[1][t][il][c]) + (s_red[2][t][il][c] + s_red[3][t][il][c]);
         };
+        // PACK: a sum of the high parts that is not finite stands alone (an
+        // infinite weight times a remainder of 0 is NaN, times the value it is not)
         auto row_sum = [&](int t, int il, int j) {
             if constexpr (!PACK) return sum4(t, il, j);
             const int c = j * g.parts;
             float v = sum4(t, il, c + 1);
             if (g.parts == 3) v += sum4(t, il, c + 2);
-            return v + sum4(t, il, c);
+            const float hi = sum4(t, il, c);
+            return (hi - hi) == 0.f ? v + hi : hi;
         };
 #pragma unroll
         for (int q = 0; q < NG; ++q) {

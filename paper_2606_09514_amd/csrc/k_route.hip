@@ -350,11 +350,16 @@ __global__ __launch_bounds__(64 * kDmWaves) void dm_kernel(GemvArgs g, int B, in
         }
         dm_step(a, v0, v1, acc, low);
     }
-    // D: lane j + 16 (i / 4), element i % 4: unit i, sequence j
+    // D: lane j + 16 (i / 4), element i % 4: unit i, sequence j.  A sum of the
+    // first parts that is not finite stands alone: an infinite weight times a
+    // remainder of 0 is NaN, times the value it is not.
 #pragma unroll
     for (int x = 0; x < kDmTiles; ++x)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s_red[wave][i][16 * x + 4 * q + e] = acc[x][e] + low[x][e];
+        for (int e = 0; e < 4; ++e) {
+            const float v = acc[x][e];
+            s_red[wave][i][16 * x + 4 * q + e] = (v - v) == 0.f ? v + low[x][e] : v;
+        }
     __syncthreads();
     for (int t = tid; t < 16 * kDmUnits; t += 64 * kDmWaves) {
         const int u = t % kDmUnits, j = t / kDmUnits;

@@ -4,8 +4,8 @@ import numpy as np
 import pytest
 import torch
 
-from _gpu import Pair
-from oracle import group_by_route
+from _gpu import Pair, gpu_step, host_weights, oracle_step
+from oracle import Oracle, group_by_route
 from paper_2606_09514_amd import lib as blib
 from paper_2606_09514_amd import synth
 from test_gpu_parity import check_prefill, gpu_prefill, gqa_shape, one_step_all
@@ -87,6 +87,56 @@ def test_packed_activation_parts(B):
     rep = one_step_all(P, hk, hv, pos, ks, x)
     print(B, rep)
     assert rep["max_hidden_err"] < (2e-6 if B <= 5 else 5e-6)
+
+
+@pytest.mark.parametrize("B,f", [(2, 11264), (5, 1024), (5, 1152), (5, 640), (8, 1152)])
+def test_infinite_weights_small_batches(B, f):
+    """Infinite weights in small batches, whose activations enter the MFMA in two or three parts: a
+    part of 0 times infinity must not turn the sum into NaN.  One infinite weight in every row of
+    the last down projection gives plus or minus infinity, as the oracle's sums do (K of whole and
+    half rounds of k-steps; 2 sequences past the rule that takes them to the MFMA)."""
+    d = 4096 if B == 2 else 256
+    shape = dict(n_layers=3, d_model=d, n_heads=d // 128, n_kv_heads=1 if d == 256 else 8, head_dim=128, d_ffn=f,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    T = 40
+    P = Pair(shape, "bf16", T, B, seed=270, omega=0.1, device_gen=d > 256)
+    rows = torch.arange(d, device="cuda")
+    P.Wd["layers"][-1]["wdown"][rows, rows * 7 % f] = float("inf")
+    P.orc = Oracle(P.cfg, *host_weights(P.Wd))
+    g = torch.Generator().manual_seed(271)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    x = synth.hidden_inputs(B, d, seed=272).numpy()
+    dk, dv = P.upload(hk.copy()), P.upload(hv.copy())
+    got, mask, _ = gpu_step(P, dk, dv, x, [T - 1] * B, [1] * B)
+    for b in range(B):
+        ref = np.asarray(oracle_step(P, hk, hv, b, T - 1, 1, x[b], route=mask[b])[0])
+        assert np.all(np.isinf(ref))
+        assert np.array_equal(got[b], ref.astype(np.float32)), (b, int(np.isnan(got[b]).sum()))
+
+
+@pytest.mark.parametrize("B", [1, 2, 17])
+def test_infinite_router_weights(B):
+    """An infinite weight of the router's first layer: infinite scores, as the oracle's.  The
+    hidden value it meets has no remainder beyond bf16, whose product with infinity is NaN."""
+    shape = dict(n_layers=6, d_model=96, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=128,
+                 dm_hidden=40, dm_act="gelu", rope_theta=1e4, rms_eps=1e-5)
+    T = 30
+    P = Pair(shape, "bf16", T, B, seed=280, omega=0.1)
+    P.Wd["dm"]["w1"][33, -5] = float("inf")
+    P.orc = Oracle(P.cfg, *host_weights(P.Wd))
+    g = torch.Generator().manual_seed(281)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    h = synth.hidden_inputs(B, 96, seed=282)
+    h[:, -5] = 1.5
+    scores = torch.zeros((B, P.L_mid), device="cuda")
+    P.gpu.pool_route(P.upload(hk), P.upload(hv), [T - 1] * B, h.cuda(), scores)
+    got = scores.cpu().numpy()
+    for b in range(B):
+        ref = np.asarray(P.orc.dm_scores(P.orc.context(hk[0, b], hv[0, b], T - 1, h[b].numpy())))
+        assert np.all(np.isinf(ref))
+        assert np.array_equal(got[b], ref.astype(np.float32)), (b, got[b], ref)
 
 
 @pytest.mark.parametrize("B,H,ctx,d,T", [(2, 8, "kv", 96, 40), (2, 136, "k+v", 96, 3000), (16, 128, "k", 3936, 70),
