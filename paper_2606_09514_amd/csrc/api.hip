@@ -167,9 +167,10 @@ bool uses_mfma(const Model& M, const Rows& rows, int batch, int K, int tok_T) {
 hipError_t launch_proj(const Model& M, int batch, int pro, int epi, GemvArgs g, hipStream_t s,
                        bool fold = false, float* fold_part = nullptr, int* gemm_fold = nullptr) {
     // prompt tokens of a prefill: the tiled GEMM
-    if (uses_gemm(M, g.rows, batch, g.K, g.tok_T))
-        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, gemm_part_elems(M.cfg, g.rows.n_max),
-                           s, gemm_fold);
+    if (uses_gemm(M, g.rows, batch, g.K, g.tok_T)) {
+        const size_t own = gemm_part_elems(M.cfg, g.rows.n_max);
+        return launch_gemm(pro, epi, g, M.gemm_tile, M.pf_split, own < M.pf_part ? own : M.pf_part, s, gemm_fold);
+    }
     if (uses_mfma(M, g.rows, batch, g.K, g.tok_T))
         return launch_mfma(pro, epi, g,
                            fold_part ? fold_part
@@ -615,7 +616,7 @@ buddy_status buddy_model_create(const buddy_config* cfg, const buddy_layer_weigh
         {(void**)&W.n_all, 4}, {(void**)&W.idx, Lm * Bc * 4 + 4}, {(void**)&W.cnt, Lm * 4 + 4},
         {(void**)&W.mask, Bc * Lm + 1}, {(void**)&W.scores, Bc * Lm * 4 + 4},
         {(void**)&W.z, Bc * din * 4}, {(void**)&W.a, Bc * c.dm_hidden * 4},
-        {(void**)&W.dm_part, Bc > 1 ? dm_part_elems(c.max_batch, c.dm_hidden) * 4 : 0},
+        {(void**)&W.dm_part, dm_part_elems(c, c.max_batch, c.dm_hidden, (int)din) * 4},
         {(void**)&W.q, Bc * qdim * 4}, {(void**)&W.o, Bc * qdim * 4},
         {(void**)&W.m, Bc * c.d_ffn * 4},
         {(void**)&W.part, Bc * c.n_heads * max_chunks * (hd + 2) * 4},
@@ -794,8 +795,10 @@ buddy_status buddy_set_budget_predictor(buddy_model* h, const buddy_predictor_we
     M.pred_a = nullptr;
     memset(&M.pred, 0, sizeof(M.pred));
     if (!p) return BUDDY_OK;
-    e = hipMalloc((void**)&M.pred_a, ((size_t)M.cfg.max_batch * p->hidden +
-                                      dm_part_elems(M.cfg.max_batch, p->hidden)) * sizeof(float));
+    const buddy_config& c = M.cfg;
+    const int din = pooled_dim(c.router_ctx, c.n_kv_heads, c.head_dim) + c.d_model;
+    e = hipMalloc((void**)&M.pred_a, ((size_t)c.max_batch * p->hidden +
+                                      dm_part_elems(c, c.max_batch, p->hidden, din)) * sizeof(float));
     if (e != hipSuccess) { M.pred_a = nullptr; return BUDDY_ENOMEM; }
     M.pred = *p;
     return BUDDY_OK;
@@ -961,7 +964,9 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
     M.pf_base = nullptr; M.pf_hlists = nullptr; M.pf_rows = 0;
     const size_t qdim = (size_t)c.n_heads * c.head_dim;
     const size_t L = c.n_layers, r16 = (rows + 15) / 16 * 16;
+    M.pf_part = gemm_part_elems(c, rows);
     struct Part { void** p; size_t bytes; } parts[] = {
+        {(void**)&M.pf_split, M.pf_part * 4},
         {(void**)&M.pf_q, rows * qdim * 4}, {(void**)&M.pf_o, rows * qdim * 4},
         {(void**)&M.pf_m, rows * (size_t)c.d_ffn * 4},
         {(void**)&M.pf_hlast, (size_t)c.max_batch * c.d_model * 4},
@@ -969,13 +974,23 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
         // prompt tokens (high and low parts)
         {(void**)&M.pf_xb, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
         {(void**)&M.pf_xb2, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
-        {(void**)&M.pf_split, gemm_part_elems(c, rows) * 4},
         {(void**)&M.pf_lists, L * rows * 4}, {(void**)&M.pf_len, (size_t)c.max_batch * 4},
         {(void**)&M.pf_groups, L * rows * 8},
     };
-    size_t total = 0;
-    for (auto& q : parts) total += (q.bytes + 255) / 256 * 256;
-    if ((e = hipMalloc(&M.pf_base, total)) != hipSuccess) { M.pf_base = nullptr; return BUDDY_ENOMEM; }
+    auto total_of = [&] {
+        size_t total = 0;
+        for (auto& q : parts) total += (q.bytes + 255) / 256 * 256;
+        return total;
+    };
+    e = hipMalloc(&M.pf_base, total_of());
+    if (e != hipSuccess && M.pf_part > gemm_part_two(c, rows)) {
+        // a device without room for the short prompts' splits: two splits only
+        (void)hipGetLastError();
+        M.pf_part = gemm_part_two(c, rows);
+        parts[0].bytes = M.pf_part * 4;
+        e = hipMalloc(&M.pf_base, total_of());
+    }
+    if (e != hipSuccess) { (void)hipGetLastError(); M.pf_base = nullptr; return BUDDY_ENOMEM; }
     M.pf_hlists = (int32_t*)malloc(L * rows * 12);   // token lists, then group pairs
     if (!M.pf_hlists) { (void)hipFree(M.pf_base); M.pf_base = nullptr; return BUDDY_ENOMEM; }
     size_t off = 0;

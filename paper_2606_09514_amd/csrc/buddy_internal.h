@@ -225,7 +225,8 @@ struct Model {
     void* pf_base; size_t pf_rows;
     float *pf_q, *pf_o, *pf_m, *pf_hlast;
     bf16_t* pf_xb, *pf_xb2;
-    float* pf_split;               // split-K partial sums, gemm_part_elems(rows)
+    float* pf_split;               // split-K partial sums, pf_part floats (gemm_part_elems)
+    size_t pf_part;
     int32_t *pf_lists, *pf_len, *pf_groups;
     int32_t* pf_hlists;            // host copy of the token lists, then of the groups
     Workspace ws;
@@ -513,10 +514,14 @@ inline int dm_slices(int B, int H, int K) {
 inline bool dm_uses_mfma(const buddy_config& c, int B, int H, int K) {
     return c.dtype == BUDDY_BF16 && B > 1 && H <= kDmMaxHidden && K % 32 == 0;
 }
-// Floats of part: slices x tiles <= 256, or one slice.
-inline size_t dm_part_elems(int max_batch, int H) {
-    const size_t few = (size_t)256 * 16 * kDmUnits, one = (size_t)max_batch * H;
-    return few > one ? few : one;
+// Floats of part for batches of up to max_batch (0: no such launch).
+inline size_t dm_part_elems(const buddy_config& c, int max_batch, int H, int K) {
+    size_t most = 0;
+    for (int B = 2; B <= max_batch; ++B) {
+        const size_t n = dm_uses_mfma(c, B, H, K) ? (size_t)dm_slices(B, H, K) * B * H : 0;
+        if (n > most) most = n;
+    }
+    return most;
 }
 // MFMA path (bf16 weights, K a multiple of 128): prep of the compact bf16
 // rows, then the MFMA projection with the same epilogues.  part: fp32
@@ -538,16 +543,33 @@ hipError_t launch_prep(int pro, const GemvArgs& g, hipStream_t s);
 hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,
                        hipStream_t s, int* fold);
 constexpr int kGemmMinRows = 64;
-// Split-K sums of a prefill of `rows` tokens: two splits of the residual-add
-// projections, or for prompts of up to kGemmShortRows tokens up to 49152
-// (splits x weight rows) per token, 128 MB at most.  It grows with rows: a
-// launch is allowed what a buffer for its own rows would hold, whatever larger
-// prompt the handle's buffer was allocated for, so that the K splits, and with
-// them the order of the sums, do not depend on earlier calls.
+// Split-K sums of a prefill of `rows` tokens (floats): two splits of the
+// residual-add projections, or for prompts of up to kGemmShortRows tokens as
+// many (splits x weight rows) per token as a projection of the model can use,
+// at most 49152 per token and 128 MB in all.  None where no projection takes
+// the tiled GEMM.  It grows with rows: a launch is allowed what a buffer for
+// its own rows would hold, whatever larger prompt the handle's buffer was
+// allocated for, so that the K splits, and with them the order of the sums, do
+// not depend on earlier calls.
 constexpr int kGemmShortRows = 1536;
+// Whether a K of `steps` steps may be split z ways: at least eight steps each,
+// whole pairs of them.
+inline bool gemm_split_ok(int steps, int z) { return steps % (2 * z) == 0 && steps / z >= 8; }
+inline size_t gemm_part_two(const buddy_config& c, size_t rows) {
+    return c.dtype == BUDDY_BF16 && rows >= (size_t)kGemmMinRows ? 2 * rows * c.d_model : 0;
+}
 inline size_t gemm_part_elems(const buddy_config& c, size_t rows) {
-    const size_t two = 2 * rows * c.d_model;
-    size_t few = rows * 49152;
+    const size_t two = gemm_part_two(c, rows);
+    if (two == 0) return 0;
+    const int qdim = c.n_heads * c.head_dim;
+    const int kn[4][2] = {{c.d_model, qdim + 2 * c.n_kv_heads * c.head_dim}, {qdim, c.d_model},
+                          {c.d_model, 2 * c.d_ffn}, {c.d_ffn, c.d_model}};
+    size_t per_row = 0;
+    for (const auto& p : kn)
+        for (int z = 2; z <= 8; z *= 2)
+            if (p[0] % 64 == 0 && gemm_split_ok(p[0] / 32, z) && (size_t)z * p[1] > per_row)
+                per_row = (size_t)z * p[1];
+    size_t few = rows * (per_row < 49152 ? per_row : 49152);
     if (few > (size_t)32 << 20) few = (size_t)32 << 20;
     return two > few ? two : few;
 }

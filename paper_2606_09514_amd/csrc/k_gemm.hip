@@ -667,8 +667,7 @@ static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t 
         for (int z = 1; z <= 8; z *= 2) {
             const dim3 grid = shape_grid<EPI>(sh, units, n);
             const int wgs = grid.x * grid.y;
-            // whole pairs of steps; K is a multiple of 64
-            if (z > 1 && (!part || steps % (2 * z) || steps / z < 8 || z * n * N > part_elems)) break;
+            if (z > 1 && (!part || !gemm_split_ok(steps, z) || z * n * N > part_elems)) break;
             if (z > 1 && !few && (EPI != EPI_ADD || sh != SH_256 || z > 2 || 2 * wgs < kCUs)) break;
             float us = grid_us(sh, wgs * z, steps / z);
             if (z > 1) us += (fold ? 0.f : 4.f) + (float)z * n * N * 8.f / 5e6f;

@@ -243,3 +243,22 @@ def test_prefill_same_bits_after_a_longer_prompt():
     fresh = prefill(x)
     prefill(other)
     assert all(torch.equal(a, b) for a, b in zip(fresh, prefill(x)))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_prefill_workspace_follows_the_model(dtype):
+    """The prefill workspace of a small model: 512 prompt rows of a few hundred values.  Its split
+    sums are those its projections can use (none in fp32, two splits of the residual adds in
+    bf16), not a wide model's 49152 floats a row (100 MB)."""
+    n = 512
+    cfg = synth.model_config("tiny", dtype, n)
+    model = blib.Model(cfg, synth.model_weights(cfg, 290, "cuda", omega=0.1), max_batch=1)
+    k, v = synth.kv_cache(cfg, 1, 0, 291, "cuda")
+    hidden = torch.randn((1, n, cfg["d_model"]), device="cuda")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    model.prefill(k, v, hidden, [n], [1])
+    grown = free - torch.cuda.mem_get_info()[0]
+    row = 4 * (2 * cfg["n_heads"] * cfg["head_dim"] + 3 * cfg["d_ffn"] + 4 * cfg["d_model"])
+    print(dtype, grown, n * row)
+    assert grown <= 4 * n * row + (8 << 20)
