@@ -108,9 +108,21 @@ const char* layer_base(const Model& M, const void* kv, int l) {
 // Qwen-7B shape B = 40, 3000 rows 1587 -> 1515; 13B MHA shape B = 1, 16000
 // rows 541 -> 523).  The count is rounded down: 520 workgroups would leave
 // most CUs waiting for the eight that run three (13B, B = 1: 560 us).
+// A chunk length holds for every sequence of the launch, so where the lengths
+// are uneven (mean_rows, the cached rows a sequence on average, under 9/10 of
+// the longest) only the long sequences have rows in every chunk: few coarse
+// chunks leave most CUs idle behind them, and one chunk more or less per
+// sequence is a large part of the work.  The longest then has at least 12
+// chunks, up to 24 while the chunks that hold rows number about 320, of at
+// least eight blocks each, and the launch at most 2048 workgroups (8-block
+// models, every block run, 512 workgroups against this, us a step: Llama-8B
+// shape, 30000 rows beside 23 of 500 2460 / 1420, 24 sequences of 2000 to 8000
+// rows 1897 / 1760, eight of 3000 to 12000 1300 / 1311; Qwen-7B shape, 6
+// blocks, 20000 rows beside 49 of 1000 1970 / 1507; 13B MHA shape, 4 blocks,
+// 16000 rows beside 4 of 500 1275 / 932).
 constexpr int kAttnMinBlocks = 2;   // workgroup blocks per chunk, at least
 
-void attn_chunks(const Model& M, int n_rows, int max_pos, int* chunks, int* chunk_len,
+void attn_chunks(const Model& M, int n_rows, int max_pos, int mean_rows, int* chunks, int* chunk_len,
                  int cap = kAttnMaxChunks) {
     const buddy_config& c = M.cfg;
     const int rows = attention_rows_per_wg(c.dtype, c.head_dim, c.n_heads / c.n_kv_heads);
@@ -127,6 +139,14 @@ void attn_chunks(const Model& M, int n_rows, int max_pos, int* chunks, int* chun
     int want = 512 / pairs;
     const int most = 256 / pairs > 32 ? 256 / pairs : 32;
     if (want > most) want = most;
+    if ((int64_t)mean_rows * 10 < (int64_t)(max_pos + 1) * 9) {
+        const int64_t busy = 320 * (int64_t)(max_pos + 1) / ((int64_t)pairs * mean_rows);
+        int fine = busy < 12 ? 12 : busy > 24 ? 24 : (int)busy;
+        const int all = (2048 + pairs - 1) / pairs;
+        if (fine > all) fine = all;
+        if (fine > blocks / 8) fine = blocks / 8;
+        if (want < fine) want = fine;
+    }
     if (want > blocks) want = blocks;
     if (want > kAttnMaxChunks) want = kAttnMaxChunks;
     if (want > cap) want = cap;
@@ -223,11 +243,12 @@ hipError_t mark(const Model& M, int kind, int l, bool stop, hipStream_t s) {
 // router's block, decode rows without an execution map, the attention also
 // writes the planner's pool sums (its chunks as the splits) when the chunks
 // fit the pool's split capacity; *pooled receives that split count, 0 if
-// it did not.
+// it did not.  mean_rows: cached rows per sequence on average, the step's
+// included (decode rows).
 buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float* hidden, int l,
                        Rows rows, int batch, int max_pos, int pos_u, const BlockBufs& bf,
                        hipStream_t s, const int32_t* groups = nullptr, int n_groups = 0,
-                       int d_upto = -1, int d_out = -1, int* pooled = nullptr) {
+                       int d_upto = -1, int d_out = -1, int* pooled = nullptr, int mean_rows = 0) {
     const buddy_config& c = M.cfg;
     const buddy_layer_weights& w = M.layers[l];
     const int qdim = c.n_heads * c.head_dim;
@@ -282,7 +303,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     } else {
         // the router's block writing the pool's sums: no more chunks than
         // the pool has splits
-        attn_chunks(M, rows.n_max, max_pos, &a.chunks, &a.chunk_len,
+        attn_chunks(M, rows.n_max, max_pos, mean_rows, &a.chunks, &a.chunk_len,
                     pooled && !exec ? M.ws.max_pool_splits : kAttnMaxChunks);
         // decode rows on the MFMA path: o goes straight to the O
         // projection's staging, split into bf16 parts as its staging would
@@ -875,9 +896,12 @@ buddy_status decode_impl(buddy_model* h, const buddy_kv* kv, float* hidden, cons
     // leaves rows out by the execution map)
     const bool fuse_pool = !route_override && !kv->pool_sum && !exec;
     int pooled = 0;
+    int64_t cached = 0;
+    for (int b = 0; b < B; ++b) cached += pos[b] + 1;
+    const int mean_rows = (int)(cached / B);
     for (int l = 0; l < S; ++l)
         if ((st = run_block(M, kv, exec, hidden, l, all, B, max_pos, pos_u, decode_bufs(M), s, nullptr,
-                            0, -1, -1, fuse_pool && l == S - 1 ? &pooled : nullptr)) != BUDDY_OK)
+                            0, -1, -1, fuse_pool && l == S - 1 ? &pooled : nullptr, mean_rows)) != BUDDY_OK)
             return st;
     // KV-aware planner and Decision Module, unless the route is given
     if (!route_override)
@@ -921,12 +945,12 @@ buddy_status decode_impl(buddy_model* h, const buddy_kv* kv, float* hidden, cons
         const Rows r{M.ws.idx + (size_t)i * c.max_batch, M.ws.cnt + i, n_max,
                      host_routed, host_routed && n_max == B};
         if ((st = run_block(M, kv, exec, hidden, l, r, B, max_pos, pos_u, decode_bufs(M), s, nullptr,
-                            0, defer ? i : -1, defer ? i : -1)) != BUDDY_OK)
+                            0, defer ? i : -1, defer ? i : -1, nullptr, mean_rows)) != BUDDY_OK)
             return st;
     }
     // last block on every sequence (it adds what the routable blocks deferred)
     st = run_block(M, kv, exec, hidden, c.n_layers - 1, all, B, max_pos, pos_u, decode_bufs(M), s,
-                   nullptr, 0, defer ? Lm : -1, -1);
+                   nullptr, 0, defer ? Lm : -1, -1, nullptr, mean_rows);
     if (M.timing.n > 0 && M.timing.next < M.timing.n) ++M.timing.next;
     M.step_end_ns = steady_ns();
     return st;

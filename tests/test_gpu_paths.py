@@ -262,3 +262,46 @@ def test_prefill_workspace_follows_the_model(dtype):
     row = 4 * (2 * cfg["n_heads"] * cfg["head_dim"] + 3 * cfg["d_ffn"] + 4 * cfg["d_model"])
     print(dtype, grown, n * row)
     assert grown <= 4 * n * row + (8 << 20)
+
+
+@pytest.mark.parametrize("G,nkv,pos", [(4, 8, [6599, 40, 0, 900, 130, 6000]), (1, 16, [5200, 5, 700, 5199]),
+                                       (2, 30, [3000, 64, 63, 128, 500, 1, 999]), (4, 12, [3299, 3290, 3280, 3150])])
+def test_uneven_lengths(G, nkv, pos):
+    """Decode over lengths on both sides of the rule for uneven ones (the mean under 9/10 of the
+    longest: 13, 10 and 5 chunks where even lengths have 10, 8 and 2; the short sequences have rows
+    in the first only)."""
+    T = max(pos) + 1
+    P = Pair(dict(gqa_shape(G), d_model=512, n_heads=G * nkv, n_kv_heads=nkv), "bf16", T, len(pos), seed=300, omega=0.1)
+    g = torch.Generator().manual_seed(301)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    x = synth.hidden_inputs(len(pos), P.cfg["d_model"], seed=302).numpy()
+    print(pos, one_step_all(P, hk, hv, pos, [b % (P.L_mid + 1) for b in range(len(pos))], x))
+
+
+def test_one_long_sequence_in_a_batch():
+    """One sequence of 16000 rows beside 23 of 100: the attention kernel may take a few times what
+    it takes for the long one alone (shared out in 32 chunks, here in 11).  With the two chunks that
+    24 such sequences of equal length have, it takes about nine times as long."""
+    B, T = 24, 16001
+    shape = dict(n_layers=3, d_model=1024, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=512,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    cfg = synth.model_config(shape, "bf16", T)
+    model = blib.Model(cfg, synth.model_weights(cfg, 310, "cuda", omega=0.1), max_batch=B)
+    k, v = (torch.zeros((3, B, 8, T, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    hidden = torch.randn((B, 1024), device="cuda")
+    hip = blib.HipEvents()
+
+    def attention_us(pos):
+        st, sp = hip.create(12), hip.create(12)
+        model.set_timing_events(blib.KERNEL_ATTENTION, cfg["n_layers"] - 1, st, sp)
+        for _ in range(12):
+            model.decode_step(k, v, hidden[:len(pos)].clone(), pos, [1] * len(pos))
+        torch.cuda.synchronize()
+        us = sorted(1e3 * hip.elapsed_ms(a, b) for a, b in zip(st, sp))
+        hip.destroy(st + sp)
+        return us[3]
+
+    alone, uneven = attention_us([T - 1]), attention_us([T - 1] + [100] * (B - 1))
+    print("alone", alone, "beside short ones", uneven)
+    assert uneven < 5 * alone
