@@ -120,10 +120,17 @@ const char* layer_base(const Model& M, const void* kv, int l) {
 // rows 1897 / 1760, eight of 3000 to 12000 1300 / 1311; Qwen-7B shape, 6
 // blocks, 20000 rows beside 49 of 1000 1970 / 1507; 13B MHA shape, 4 blocks,
 // 16000 rows beside 4 of 500 1275 / 932).
+// Of a device-routed block's n_rows sequences only about run_rows run, and
+// their chunks alone number about 256 (at most 2048 workgroups again), so that
+// most CUs have one (8-block models, us a step, 512 workgroups whatever the
+// budgets / this: Llama-8B shape, 24 sequences of 16000 rows, a sixth of the
+// routable blocks each 2080 / 1788, a third 2155 / 2094, half 2255 / 2254; 18 of
+// 6000 rows 1273 / 1199, 1310 / 1280, 1367 / 1357; Qwen-7B shape, 6 blocks, 50
+// of 8000 rows, a quarter 1531 / 1480).
 constexpr int kAttnMinBlocks = 2;   // workgroup blocks per chunk, at least
 
-void attn_chunks(const Model& M, int n_rows, int max_pos, int mean_rows, int* chunks, int* chunk_len,
-                 int cap = kAttnMaxChunks) {
+void attn_chunks(const Model& M, int n_rows, int run_rows, int max_pos, int mean_rows, int* chunks,
+                 int* chunk_len, int cap = kAttnMaxChunks) {
     const buddy_config& c = M.cfg;
     const int rows = attention_rows_per_wg(c.dtype, c.head_dim, c.n_heads / c.n_kv_heads);
     const int blocks = (max_pos + 1 + rows - 1) / rows;
@@ -136,13 +143,15 @@ void attn_chunks(const Model& M, int n_rows, int max_pos, int mean_rows, int* ch
         *chunks = 1;
         return;
     }
+    const int all = (2048 + pairs - 1) / pairs;
     int want = 512 / pairs;
+    const int running = 256 / (run_rows * c.n_kv_heads);
+    if (want < running) want = running < all ? running : all;
     const int most = 256 / pairs > 32 ? 256 / pairs : 32;
     if (want > most) want = most;
     if ((int64_t)mean_rows * 10 < (int64_t)(max_pos + 1) * 9) {
         const int64_t busy = 320 * (int64_t)(max_pos + 1) / ((int64_t)pairs * mean_rows);
         int fine = busy < 12 ? 12 : busy > 24 ? 24 : (int)busy;
-        const int all = (2048 + pairs - 1) / pairs;
         if (fine > all) fine = all;
         if (fine > blocks / 8) fine = blocks / 8;
         if (want < fine) want = fine;
@@ -244,11 +253,13 @@ hipError_t mark(const Model& M, int kind, int l, bool stop, hipStream_t s) {
 // writes the planner's pool sums (its chunks as the splits) when the chunks
 // fit the pool's split capacity; *pooled receives that split count, 0 if
 // it did not.  mean_rows: cached rows per sequence on average, the step's
-// included (decode rows).
+// included; run_rows: how many of the rows are expected to run the block
+// (0: all of them; decode rows).
 buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float* hidden, int l,
                        Rows rows, int batch, int max_pos, int pos_u, const BlockBufs& bf,
                        hipStream_t s, const int32_t* groups = nullptr, int n_groups = 0,
-                       int d_upto = -1, int d_out = -1, int* pooled = nullptr, int mean_rows = 0) {
+                       int d_upto = -1, int d_out = -1, int* pooled = nullptr, int mean_rows = 0,
+                       int run_rows = 0) {
     const buddy_config& c = M.cfg;
     const buddy_layer_weights& w = M.layers[l];
     const int qdim = c.n_heads * c.head_dim;
@@ -303,7 +314,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
     } else {
         // the router's block writing the pool's sums: no more chunks than
         // the pool has splits
-        attn_chunks(M, rows.n_max, max_pos, mean_rows, &a.chunks, &a.chunk_len,
+        attn_chunks(M, rows.n_max, run_rows ? run_rows : rows.n_max, max_pos, mean_rows, &a.chunks, &a.chunk_len,
                     pooled && !exec ? M.ws.max_pool_splits : kAttnMaxChunks);
         // decode rows on the MFMA path: o goes straight to the O
         // projection's staging, split into bf16 parts as its staging would
@@ -927,6 +938,15 @@ buddy_status decode_impl(buddy_model* h, const buddy_kv* kv, float* hidden, cons
     // the sums, their order and the residual add are those of the add kernel
     const bool defer = M.ws.down_part && uses_mfma(M, all, B, c.d_model, 0) &&
                        uses_mfma(M, all, B, c.d_ffn, 0);
+    // device-routed: a routable block is expected to run on the batch's share
+    // of the budgets, or on a third of it where the host has none
+    int run_rows = 0;
+    if (!host_routed && Lm > 0) {
+        int64_t sum = 0;
+        for (int b = 0; b < B && k && !route_override && !predict; ++b) sum += k[b];
+        run_rows = !k || route_override || predict ? (B + 2) / 3 : (int)((sum + Lm - 1) / Lm);
+        if (run_rows < 1) run_rows = 1;
+    }
     for (int l = S; l < S + Lm; ++l) {
         const int i = l - S;
         int n_max = B;
@@ -945,7 +965,7 @@ buddy_status decode_impl(buddy_model* h, const buddy_kv* kv, float* hidden, cons
         const Rows r{M.ws.idx + (size_t)i * c.max_batch, M.ws.cnt + i, n_max,
                      host_routed, host_routed && n_max == B};
         if ((st = run_block(M, kv, exec, hidden, l, r, B, max_pos, pos_u, decode_bufs(M), s, nullptr,
-                            0, defer ? i : -1, defer ? i : -1, nullptr, mean_rows)) != BUDDY_OK)
+                            0, defer ? i : -1, defer ? i : -1, nullptr, mean_rows, run_rows)) != BUDDY_OK)
             return st;
     }
     // last block on every sequence (it adds what the routable blocks deferred)

@@ -279,6 +279,19 @@ def test_uneven_lengths(G, nkv, pos):
     print(pos, one_step_all(P, hk, hv, pos, [b % (P.L_mid + 1) for b in range(len(pos))], x))
 
 
+def attention_us(model, layer, k, v, hidden, pos):
+    """Time of a block's attention score kernel in steps with a budget of 1, microseconds."""
+    hip = blib.HipEvents()
+    st, sp = hip.create(12), hip.create(12)
+    model.set_timing_events(blib.KERNEL_ATTENTION, layer, st, sp)
+    for _ in range(12):
+        model.decode_step(k, v, hidden[:len(pos)].clone(), pos, [1] * len(pos))
+    torch.cuda.synchronize()
+    us = sorted(1e3 * hip.elapsed_ms(a, b) for a, b in zip(st, sp))
+    hip.destroy(st + sp)
+    return us[3]
+
+
 def test_one_long_sequence_in_a_batch():
     """One sequence of 16000 rows beside 23 of 100: the attention kernel may take a few times what
     it takes for the long one alone (shared out in 32 chunks, here in 11).  With the two chunks that
@@ -290,18 +303,29 @@ def test_one_long_sequence_in_a_batch():
     model = blib.Model(cfg, synth.model_weights(cfg, 310, "cuda", omega=0.1), max_batch=B)
     k, v = (torch.zeros((3, B, 8, T, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
     hidden = torch.randn((B, 1024), device="cuda")
-    hip = blib.HipEvents()
-
-    def attention_us(pos):
-        st, sp = hip.create(12), hip.create(12)
-        model.set_timing_events(blib.KERNEL_ATTENTION, cfg["n_layers"] - 1, st, sp)
-        for _ in range(12):
-            model.decode_step(k, v, hidden[:len(pos)].clone(), pos, [1] * len(pos))
-        torch.cuda.synchronize()
-        us = sorted(1e3 * hip.elapsed_ms(a, b) for a, b in zip(st, sp))
-        hip.destroy(st + sp)
-        return us[3]
-
-    alone, uneven = attention_us([T - 1]), attention_us([T - 1] + [100] * (B - 1))
+    alone = attention_us(model, 2, k, v, hidden, [T - 1])
+    uneven = attention_us(model, 2, k, v, hidden, [T - 1] + [100] * (B - 1))
     print("alone", alone, "beside short ones", uneven)
     assert uneven < 5 * alone
+
+
+def test_block_that_few_sequences_run():
+    """A device-routed block that few of 24 sequences of 8000 rows run (each runs one of six): its
+    attention may take a few times what one sequence alone takes in 32 chunks; with the two chunks
+    that suit 24 running sequences it takes five times as long."""
+    B, T = 24, 8001
+    shape = dict(n_layers=8, d_model=1024, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=512,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    cfg = synth.model_config(shape, "bf16", T)
+    model = blib.Model(cfg, synth.model_weights(cfg, 320, "cuda"), max_batch=B)
+    k, v = (torch.zeros((8, B, 8, T, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    gen = torch.Generator(device="cuda").manual_seed(321)
+    hidden = torch.randn((B, 1024), generator=gen, device="cuda")
+    mask = torch.zeros((B, 6), dtype=torch.uint8, device="cuda")
+    model.decode_step(k, v, hidden.clone(), [T - 1] * B, [1] * B, mask_out=mask)
+    runs = mask.sum(0).tolist()
+    block = min((n, i) for i, n in enumerate(runs) if n > 0)[1]
+    alone = attention_us(model, 7, k, v, hidden, [T - 1])
+    few = attention_us(model, 1 + block, k, v, hidden, [T - 1] * B)
+    print("runs", runs, "alone", alone, "few", few)
+    assert runs[block] <= 4 and few < 2.5 * alone
