@@ -359,9 +359,10 @@ buddy_status buddy_set_launch_policy(buddy_model* m, int32_t policy);
  *   BUDDY_GEMM_TILE_128, BUDDY_GEMM_TILE_256: always that tile (weight
  *     rows x token rows), K never split;
  *   BUDDY_GEMM_TILE_256_SPLIT: 256 x 256, K split in two for the
- *     residual-add projections (where K is a multiple of 128).
- * The tiles without a split give the same results bit for bit; a split
- * adds the two half sums, a different rounding order. */
+ *     residual-add projections (on 128 x 128 tiles where K is not a multiple
+ *     of 128).
+ * The tiles without a split give the same results bit for bit; a split adds
+ * its two to eight partial sums, a different rounding order. */
 typedef enum {
     BUDDY_GEMM_TILE_AUTO = 0,
     BUDDY_GEMM_TILE_128 = 1,

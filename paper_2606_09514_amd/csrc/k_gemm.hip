@@ -686,8 +686,11 @@ static hipError_t launch_gemm_epi(const GemvArgs& g, int units, int tile, float*
     const int n = g.rows.n_max;
     if (tile == BUDDY_GEMM_TILE_AUTO) return launch_auto<EPI>(g, units, part, part_elems, s, fold);
     if (tile == BUDDY_GEMM_TILE_128) return launch_shape<EPI>(SH_128, 1, g, units, n, nullptr, s, false, fold);
-    const bool split = tile == BUDDY_GEMM_TILE_256_SPLIT && EPI == EPI_ADD && part && (g.K / kTileK) % 4 == 0;
-    return launch_shape<EPI>(SH_256, split ? 2 : 1, g, units, n, part, s, false, fold);
+    if (tile != BUDDY_GEMM_TILE_256_SPLIT || EPI != EPI_ADD || !part)
+        return launch_shape<EPI>(SH_256, 1, g, units, n, nullptr, s, false, fold);
+    // halves of an odd number of steps: the 128 x 128 tile, which takes its
+    // weights step by step, gives the same sums
+    return launch_shape<EPI>((g.K / kTileK) % 4 == 0 ? SH_256 : SH_128, 2, g, units, n, part, s, false, fold);
 }
 
 hipError_t launch_gemm(int pro, int epi, const GemvArgs& g, int tile, float* part, size_t part_elems,

@@ -329,3 +329,22 @@ def test_block_that_few_sequences_run():
     few = attention_us(model, 1 + block, k, v, hidden, [T - 1] * B)
     print("runs", runs, "alone", alone, "few", few)
     assert runs[block] <= 4 and few < 2.5 * alone
+
+
+def test_split_tile_of_any_k():
+    """GEMM_TILE_256_SPLIT splits K of the residual adds wherever the tiled GEMM runs: with K of an odd
+    number of 64s (576 and 2240 here) too, on the 128 x 128 tile.  Other bits than the unsplit tile, from
+    the order of the sums alone (1e-2 of the largest output, as for the short prompts)."""
+    n, f = 200, 2240
+    shape = dict(n_layers=3, d_model=576, n_heads=9, n_kv_heads=3, head_dim=64, d_ffn=f,
+                 dm_hidden=64, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    P = Pair(shape, "bf16", n, 1, seed=330, omega=0.1)
+    out = {}
+    for tile in (blib.GEMM_TILE_128, blib.GEMM_TILE_256, blib.GEMM_TILE_256_SPLIT, blib.GEMM_TILE_AUTO):
+        P.gpu.set_gemm_tile(tile)
+        out[tile] = gpu_prefill(P, [n], [1], n, seed=331)[0][0, :n]
+    plain, split = out[blib.GEMM_TILE_128], out[blib.GEMM_TILE_256_SPLIT]
+    assert np.array_equal(plain, out[blib.GEMM_TILE_256])
+    assert not np.array_equal(plain, split)
+    for a in (split, out[blib.GEMM_TILE_AUTO]):
+        assert np.max(np.abs(a - plain)) <= 1e-2 * np.max(np.abs(plain))
