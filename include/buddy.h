@@ -311,7 +311,12 @@ buddy_status buddy_decode_step_auto(buddy_model* m, const buddy_kv* kv, float* h
  *   k:      host [B] budgets 0..L_mid (ignored with route_override).
  *   route_override, mask_out, scores_out: as buddy_decode_step.
  * Rows of all prompts together: B * t_stride <= 65535.  Grows the handle's
- * prefill workspace when needed and returns after the device has finished
+ * prefill workspace when needed: for each row of the largest call so far
+ * 8 n_heads head_dim + 4 d_ffn bytes of activations, 8 times the widest of
+ * d_model, d_ffn, n_heads head_dim and the router input in staged ones,
+ * 12 n_layers of lists and, in bf16 from 64 rows on, 8 d_model bytes of partial
+ * sums or, if that is more and the device has room, those of up to eight K
+ * splits (at most 192 KiB a row and 128 MiB in all).  Returns after the device has finished
  * (the host waits for the route to build the per-block token lists). */
 buddy_status buddy_prefill(buddy_model* m, const buddy_kv* kv, float* hidden, int32_t t_stride,
                            const int32_t* len, const int32_t* k, int32_t B, int32_t skip_kv,
