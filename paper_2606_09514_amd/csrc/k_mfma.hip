@@ -5,9 +5,8 @@
 //  prep_kernel  writes the routed rows in MFMA operand order (row i of the
 //               launch is sequence idx[i]) as bf16 high and low parts
 //               (xbs_index; three or two parts in one fragment for small
-//               batches, xbp_index): RMSNorm and gain folded in (PRO_RMSNORM), the
-//               router context built from the pool's split sums (PRO_POOL), or
-//               a plain conversion (PRO_NONE).  Inputs staged by their
+//               batches, xbp_index): RMSNorm and gain folded in (PRO_RMSNORM)
+//               or a plain conversion (PRO_NONE).  Inputs staged by their
 //               producer (PRO_STAGED: the attention output, the SwiGLU output)
 //               skip it.
 //  mfma_kernel  Y = W XB^T with v_mfma_f32_16x16x32_bf16 (fp32 accumulate),
@@ -112,22 +111,13 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(GemvArgs g, int n_ho
                              ((s_ss[4] + s_ss[5]) + (s_ss[6] + s_ss[7]));
         inv = 1.0f / sqrtf(ss_all / (float)K + g.eps);
     }
-    const float inv_n = PRO == PRO_POOL ? 1.0f / (float)(seq_pos(g.pos, g.pos_u, b) + 1) : 0.f;
-    const int zdim = pooled_dim(g.ctx, g.nkv, g.hd);
     for (int k = tid * 8; k < K; k += kPrepThreads * 8) {
         float v[8];
-        if (PRO == PRO_POOL && k < zdim) {
-            const float4 t0 = pooled_feature4(g, b, k, inv_n), t1 = pooled_feature4(g, b, k + 4, inv_n);
-            v[0] = t0.x; v[1] = t0.y; v[2] = t0.z; v[3] = t0.w;
-            v[4] = t1.x; v[5] = t1.y; v[6] = t1.z; v[7] = t1.w;
-        } else {
-            const float* x = PRO == PRO_POOL ? g.h + (size_t)b * g.d + (k - zdim)
-                                             : g.X + (size_t)b * g.ldx + k;
-            const float4 t0 = *reinterpret_cast<const float4*>(x);
-            const float4 t1 = *reinterpret_cast<const float4*>(x + 4);
-            v[0] = t0.x; v[1] = t0.y; v[2] = t0.z; v[3] = t0.w;
-            v[4] = t1.x; v[5] = t1.y; v[6] = t1.z; v[7] = t1.w;
-        }
+        const float* x = g.X + (size_t)b * g.ldx + k;
+        const float4 t0 = *reinterpret_cast<const float4*>(x);
+        const float4 t1 = *reinterpret_cast<const float4*>(x + 4);
+        v[0] = t0.x; v[1] = t0.y; v[2] = t0.z; v[3] = t0.w;
+        v[4] = t1.x; v[5] = t1.y; v[6] = t1.z; v[7] = t1.w;
         if (PRO == PRO_RMSNORM) {
             float gv[8];
             St<bf16_t>::vec((const bf16_t*)g.gain + k, gv);
@@ -623,8 +613,8 @@ static hipError_t launch_mfma_epi(const GemvArgs& g, int units, int n_host, floa
 hipError_t launch_prep(int pro, const GemvArgs& g, hipStream_t s) {
     const int n_host = g.rows.exact ? g.rows.n_max : -1;
     if (pro == PRO_RMSNORM) prep_kernel<PRO_RMSNORM><<<g.rows.n_max, kPrepThreads, 0, s>>>(g, n_host);
-    else if (pro == PRO_POOL) prep_kernel<PRO_POOL><<<g.rows.n_max, kPrepThreads, 0, s>>>(g, n_host);
-    else prep_kernel<PRO_NONE><<<g.rows.n_max, kPrepThreads, 0, s>>>(g, n_host);
+    else if (pro == PRO_NONE) prep_kernel<PRO_NONE><<<g.rows.n_max, kPrepThreads, 0, s>>>(g, n_host);
+    else return hipErrorInvalidValue;   // the router's first layer has kernels of its own
     return hipGetLastError();
 }
 
@@ -636,7 +626,7 @@ hipError_t launch_mfma(int pro, int epi, const GemvArgs& g, float* part, hipStre
     }
     if (epi == EPI_QKV) return launch_mfma_epi<EPI_QKV>(g, (g.nq + 2 * g.nkv) * (g.hd / 2), n_host, part, s);
     if (epi == EPI_SWIGLU) return launch_mfma_epi<EPI_SWIGLU>(g, g.f, n_host, part, s);
-    if (epi == EPI_BIAS_ACT) return launch_mfma_epi<EPI_BIAS_ACT>(g, g.N, n_host, part, s);
+    if (epi != EPI_ADD) return hipErrorInvalidValue;
     if (fold && (!part || pro != PRO_STAGED)) return hipErrorInvalidValue;
     return launch_mfma_epi<EPI_ADD>(g, g.N, n_host, part, s, fold);
 }
