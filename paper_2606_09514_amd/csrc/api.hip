@@ -1010,7 +1010,6 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
     const size_t L = c.n_layers, r16 = (rows + 15) / 16 * 16;
     M.pf_part = gemm_part_elems(c, rows);
     struct Part { void** p; size_t bytes; } parts[] = {
-        {(void**)&M.pf_split, M.pf_part * 4},
         {(void**)&M.pf_q, rows * qdim * 4}, {(void**)&M.pf_o, rows * qdim * 4},
         {(void**)&M.pf_m, rows * (size_t)c.d_ffn * 4},
         {(void**)&M.pf_hlast, (size_t)c.max_batch * c.d_model * 4},
@@ -1018,6 +1017,7 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
         // prompt tokens (high and low parts)
         {(void**)&M.pf_xb, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
         {(void**)&M.pf_xb2, 2 * r16 * (size_t)M.ws.xb_ld * sizeof(bf16_t)},
+        {(void**)&M.pf_split, M.pf_part * 4},
         {(void**)&M.pf_lists, L * rows * 4}, {(void**)&M.pf_len, (size_t)c.max_batch * 4},
         {(void**)&M.pf_groups, L * rows * 8},
     };
@@ -1031,7 +1031,8 @@ buddy_status ensure_prefill_ws(Model& M, size_t rows) {
         // a device without room for the short prompts' splits: two splits only
         (void)hipGetLastError();
         M.pf_part = gemm_part_two(c, rows);
-        parts[0].bytes = M.pf_part * 4;
+        for (auto& q : parts)
+            if (q.p == (void**)&M.pf_split) q.bytes = M.pf_part * 4;
         e = hipMalloc(&M.pf_base, total_of());
     }
     if (e != hipSuccess) { (void)hipGetLastError(); M.pf_base = nullptr; return BUDDY_ENOMEM; }
