@@ -53,7 +53,8 @@ class Pair:
     @property
     def path(self):
         """Projection path the library takes at this batch: the GEMV (fp32
-        activations) up to four sequences or in fp32, the MFMA path beyond."""
+        activations) up to four sequences or in fp32, the MFMA path beyond
+        (for wide models from two sequences on, with 24-bit activations)."""
         return "mfma" if self.cfg["dtype"] == "bf16" and self.batch > 4 else "gemv"
 
     def empty_host_cache(self):

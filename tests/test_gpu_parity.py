@@ -661,8 +661,8 @@ def test_prefill_gemm_tail_round():
     """A gate/up grid two rounds and a bit of 256 x 256 tiles on 256 CUs
     (8704 units x 2000 prompt rows: 68 x 8 = 544 tiles): the automatic
     choice keeps 512 of them on 256 x 256 tiles and sends the last 512 units
-    to a 128 x 128 launch.  Every output accumulates over K in the same order
-    in both tiles, so the prefill equals the all-128 x 128 and all-256 x 256
+    to a 128 x 256 launch.  Every output accumulates over K in the same order
+    in every tile, so the prefill equals the all-128 x 128 and all-256 x 256
     runs bit for bit (outputs, routes and caches); both of those are held to
     the oracle by the tests above."""
     shape = dict(n_layers=4, d_model=256, n_heads=4, n_kv_heads=1, head_dim=128, d_ffn=8704,

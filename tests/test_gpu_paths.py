@@ -348,3 +348,29 @@ def test_split_tile_of_any_k():
     assert not np.array_equal(plain, split)
     for a in (split, out[blib.GEMM_TILE_AUTO]):
         assert np.max(np.abs(a - plain)) <= 1e-2 * np.max(np.abs(plain))
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_non_finite_router_context(bad):
+    """A value that is not finite in one sequence's router context, whose remainders beyond bf16 do
+    not exist: that sequence's scores are the oracle's (infinite or NaN), and the others', in the
+    same MFMA tile, are as accurate as without it."""
+    B, T = 6, 30
+    shape = dict(n_layers=6, d_model=96, n_heads=2, n_kv_heads=2, head_dim=64, d_ffn=128,
+                 dm_hidden=40, dm_act="silu", rope_theta=1e4, rms_eps=1e-5)
+    P = Pair(shape, "bf16", T, B, seed=340, omega=0.1)
+    g = torch.Generator().manual_seed(341)
+    hk = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    hv = synth.storage_numpy(torch.randn(P.shape5, generator=g).to(P.tdt))
+    h = synth.hidden_inputs(B, 96, seed=342)
+    h[2, 7] = bad
+    scores = torch.zeros((B, P.L_mid), device="cuda")
+    P.gpu.pool_route(P.upload(hk), P.upload(hv), [T - 1] * B, h.cuda(), scores)
+    got = scores.cpu().numpy()
+    for b in range(B):
+        ref = np.asarray(P.orc.dm_scores(P.orc.context(hk[0, b], hv[0, b], T - 1, h[b].numpy())))
+        if b == 2:
+            assert not np.any(np.isfinite(ref))
+            assert np.array_equal(got[b], ref.astype(np.float32), equal_nan=True), (got[b], ref)
+        else:
+            assert np.max(np.abs(got[b] - ref)) <= 1e-5 * max(1.0, float(np.max(np.abs(ref)))), b
