@@ -188,14 +188,14 @@ __host__ __device__ constexpr int mfma_lds_bytes(int rt, int nt, int gt, int kr 
 // weight loads are pending).  The k-steps enter the accumulators in the
 // same order for either round length, so the sums are identical bit for bit.
 // KR = 4 needs a multiple of four k-steps per wavefront (no partial round).
-// PACK: the packed activations of a small batch (xbp_index; NT = 1): one
-// fragment and one MFMA per weight tile and k-step; a row's sum is that of
-// its g.parts columns, the smallest part first.
-template <int EPI, int NT, int RT, int KR = 2, bool PACK = false>
+// PACK > 0: the packed activations of a small batch in that many parts
+// (xbp_index; NT = 1): one fragment and one MFMA per weight tile and k-step; a
+// row's sum is that of its PACK columns, the smallest part first.
+template <int EPI, int NT, int RT, int KR = 2, int PACK = 0>
 __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_host, float* part,
                                                    int fold) {
     static_assert(KR == 2 || KR == 4, "rounds of two or four k-steps");
-    static_assert(!PACK || NT == 1, "packed rows fill one column tile");
+    static_assert(PACK == 0 || ((PACK == 2 || PACK == 3) && NT == 1), "packed rows fill one column tile");
     constexpr int FR = PACK ? 1 : 2;          // fragments per column tile and k-step
     constexpr bool kPaired = EPI == EPI_SWIGLU || EPI == EPI_QKV;
     constexpr int GT = kPaired ? 2 : 1;       // weight tiles per epilogue group
@@ -274,16 +274,23 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         for (int c = 0; c < NT; ++c)
             Bp[c] = g.XB + (((size_t)((j0 >> 4) + min(c, nct - 1)) * S + kw) * (64 * FR) + lane) * 8;
 
-        // PACK: even and odd k-steps accumulate apart (shorter chains of fp32
-        // additions: the GEMV that small batches took before sums 64 lanes'
-        // short chains as a tree)
+        // PACK: even and odd k-steps accumulate apart, and with three parts
+        // (24 bits) the sums move to `done` every eight k-steps.  The error of
+        // an MFMA chain grows with its length: 16 steps in a row left the hidden
+        // state further from float64 than the GEMV that these batches took
+        // before (rms over 30 seeds, three blocks, 9000 cached rows: Llama-8B
+        // shape, B = 4 5.00e-7 against 4.13e-7, now 3.97e-7; Qwen-7B shape, B = 3
+        // 4.65e-7, 4.15e-7, 3.75e-7; 13B MHA shape, B = 3 5.4e-7, 3.8e-7, 3.7e-7),
+        // for 2 % of the step (8 blocks, B = 4 882 -> 897 us; GEMV 1549).  Two
+        // parts (16 bits) are further off than either by far.
         constexpr int NA = PACK ? 2 : 1;
-        f32x4_t acc[RT][NT], odd[PACK ? RT : 1];
+        f32x4_t acc[RT][NT], odd[PACK ? RT : 1], done[PACK == 3 ? RT : 1];
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
 #pragma unroll
             for (int c = 0; c < NT; ++c) acc[t][c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
             if (PACK) odd[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            if (PACK == 3) done[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
         }
 
         if (j0 > 0) __syncthreads();   // the previous group's epilogue is done with the LDS
@@ -298,7 +305,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                 for (int c = 0; c < NT; ++c) {
                     const bf16_t* bp = Bp[c] + 512 * FR * (KR * r + (half ? 0 : u));
                     // reads data no kernel writes while this one runs: no memory clobber
-                    if constexpr (PACK)
+                    if constexpr (PACK > 0)
                         asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(bv[u][0][c]) : "v"(bp));
                     else
                         asm volatile("global_load_dwordx4 %0, %2, off\n\t"
@@ -339,7 +346,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
             // a half round's second k-step multiplies zeros (adds exactly 0):
             // the MFMAs stay unconditional.  PACK leaves it out instead: the
             // weights there are copies, and an infinite one times 0 is NaN
-            if constexpr (KR == 2 && !PACK) {
+            if constexpr (KR == 2 && PACK == 0) {
                 const uint32_t keep = half ? 0u : ~0u;
 #pragma unroll
                 for (int c = 0; c < NT; ++c)
@@ -361,10 +368,22 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
                                 __builtin_bit_cast(bf16x8_t, bv[u][p][c]), to, 0, 0, 0);
                         }
             }
-        }
-        if constexpr (PACK) {
+            if constexpr (PACK == 3) {
+                if (((r + 1) * KR) % 8 == 0) {
 #pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t][0] += odd[t];
+                    for (int t = 0; t < RT; ++t) {
+                        done[t] += acc[t][0] + odd[t];
+                        acc[t][0] = odd[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+            }
+        }
+        if constexpr (PACK > 0) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                acc[t][0] += odd[t];
+                if (PACK == 3) acc[t][0] += done[t];
+            }
         }
 
         // per epilogue group: reduce the four K-slices through LDS, then the
@@ -376,10 +395,10 @@ __global__ __launch_bounds__(256) void mfma_kernel(GemvArgs g, int units, int n_
         // PACK: a sum of the high parts that is not finite stands alone (an
         // infinite weight times a remainder of 0 is NaN, times the value it is not)
         auto row_sum = [&](int t, int il, int j) {
-            if constexpr (!PACK) return sum4(t, il, j);
-            const int c = j * g.parts;
+            if constexpr (PACK == 0) return sum4(t, il, j);
+            const int c = j * PACK;
             float v = sum4(t, il, c + 1);
-            if (g.parts == 3) v += sum4(t, il, c + 2);
+            if (PACK == 3) v += sum4(t, il, c + 2);
             const float hi = sum4(t, il, c);
             return (hi - hi) == 0.f ? v + hi : hi;
         };
@@ -474,7 +493,7 @@ __global__ __launch_bounds__(256) void split_add_kernel(GemvArgs g, int units, i
 
 // One instantiation's launch; LDS beyond the 64 KB default (eight weight
 // tiles per workgroup, or four-k-step rounds) is allowed once per device.
-template <int EPI, int NT, int RT, int KR, bool PACK = false>
+template <int EPI, int NT, int RT, int KR, int PACK = 0>
 static hipError_t launch_tiles(dim3 grid, const GemvArgs& g, int units, int n_host, float* part,
                                int fold, hipStream_t s) {
     constexpr int kGT = EPI == EPI_SWIGLU || EPI == EPI_QKV ? 2 : 1;
@@ -506,7 +525,8 @@ static hipError_t launch_mfma_rounds(const GemvArgs& g, int units, int n_host, i
     const dim3 grid((units + per - 1) / per, splits);
     const int tiles = (g.rows.n_max + 15) / 16;
     hipError_t e;
-    if (g.parts) e = launch_tiles<EPI, 1, RT, KR, true>(grid, g, units, n_host, part, fold, s);
+    if (g.parts == 3) e = launch_tiles<EPI, 1, RT, KR, 3>(grid, g, units, n_host, part, fold, s);
+    else if (g.parts == 2) e = launch_tiles<EPI, 1, RT, KR, 2>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 1) e = launch_tiles<EPI, 1, RT, KR>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 2) e = launch_tiles<EPI, 2, RT, KR>(grid, g, units, n_host, part, fold, s);
     else if (tiles <= 3) e = launch_tiles<EPI, 3, RT, KR>(grid, g, units, n_host, part, fold, s);
