@@ -127,10 +127,15 @@ const char* layer_base(const Model& M, const void* kv, int l) {
 // routable blocks each 2080 / 1788, a third 2155 / 2094, half 2255 / 2254; 18 of
 // 6000 rows 1273 / 1199, 1310 / 1280, 1367 / 1357; Qwen-7B shape, 6 blocks, 50
 // of 8000 rows, a quarter 1531 / 1480).
+// The router's block of a single sequence, whose chunk sums are also the
+// pool's splits (pool), keeps the 2048: a chunk's sum is one chain, and with 32
+// chunks instead of 64 the scores of 30000 rows were 2.8e-7 off instead of
+// 2.0e-7 (geometric mean over 60 seeds, pooled context alone), for 4 us in that
+// one block.  In a batch the first layer's fp64 slice sums gain more than that.
 constexpr int kAttnMinBlocks = 2;   // workgroup blocks per chunk, at least
 
 void attn_chunks(const Model& M, int n_rows, int run_rows, int max_pos, int mean_rows, int* chunks,
-                 int* chunk_len, int cap = kAttnMaxChunks) {
+                 int* chunk_len, bool pool, int cap) {
     const buddy_config& c = M.cfg;
     const int rows = attention_rows_per_wg(c.dtype, c.head_dim, c.n_heads / c.n_kv_heads);
     const int blocks = (max_pos + 1 + rows - 1) / rows;
@@ -156,6 +161,7 @@ void attn_chunks(const Model& M, int n_rows, int run_rows, int max_pos, int mean
         if (fine > blocks / 8) fine = blocks / 8;
         if (want < fine) want = fine;
     }
+    if (pool && n_rows == 1) want = all;
     if (want > blocks) want = blocks;
     if (want > kAttnMaxChunks) want = kAttnMaxChunks;
     if (want > cap) want = cap;
@@ -315,7 +321,7 @@ buddy_status run_block(Model& M, const buddy_kv* kv, const uint8_t* exec, float*
         // the router's block writing the pool's sums: no more chunks than
         // the pool has splits
         attn_chunks(M, rows.n_max, run_rows ? run_rows : rows.n_max, max_pos, mean_rows, &a.chunks, &a.chunk_len,
-                    pooled && !exec ? M.ws.max_pool_splits : kAttnMaxChunks);
+                    pooled && !exec, pooled && !exec ? M.ws.max_pool_splits : kAttnMaxChunks);
         // decode rows on the MFMA path: o goes straight to the O
         // projection's staging, split into bf16 parts as its staging would
         if (uses_mfma(M, rows, batch, qdim, 0)) a.xb_out = bf.xb;
