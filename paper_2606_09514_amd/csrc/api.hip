@@ -192,9 +192,13 @@ bool uses_mfma(const Model& M, const Rows& rows, int batch, int K, int tok_T) {
 }
 
 // A routed projection: the GEMV for small batches (mfma_batch) or fp32
-// weights, the MFMA path beyond.  The choice depends on the batch, not on how
-// many sequences a block routes, so a sequence's arithmetic does not depend
-// on the routes of the others or on the launch policy.
+// weights, the MFMA path beyond.  In a decode step the choice depends on the
+// batch, not on how many sequences a block routes, so a sequence's projections
+// do not depend on the routes of the others or on the launch policy (the
+// attention's chunk bounds follow the rows that a launch is sized for).  In a
+// prefill the tokens that run a block decide its path, and on the tiled GEMM
+// the K splits, so what a prompt is batched with can change the order of its
+// sums.
 // fold: the MFMA path's residual add goes to the partial buffer for the next
 // staging to add (the caller has checked that the buffer holds the rows):
 // fold_part, or the handle's K-split buffer.  gemm_fold: the same for the

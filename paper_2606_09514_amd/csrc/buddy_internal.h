@@ -297,8 +297,8 @@ inline int pool_max_splits(int max_ctx) {
 }
 
 // Split sums of the first layer's K/V rows 0..pos; returns the number of
-// splits per (sequence, KV head) in *splits (the Decision Module GEMV folds
-// them, PRO_POOL).
+// splits per (sequence, KV head) in *splits (the Decision Module's first layer
+// folds them: dm_kernel, or the GEMV's PRO_POOL).
 hipError_t launch_pool(const Model& M, const void* k0, const void* v0, int B, int max_pos,
                        int pos_u, int* splits, hipStream_t s);
 // The same context from running sums (buddy_kv.pool_sum / pool_rows): adds
@@ -551,6 +551,12 @@ constexpr int kGemmMinRows = 64;
 // its own rows would hold, whatever larger prompt the handle's buffer was
 // allocated for, so that the K splits, and with them the order of the sums, do
 // not depend on earlier calls.
+// The limit: beyond it the estimate alone (no limit) was equal or little
+// better (four blocks, every one run, us, limit / none: Llama-8B shape, 1600
+// tokens 3485 / 3400, 1800 3545 / 3560, 2300 4357 / 4370, 2700 5250 / 5290;
+// Qwen-7B shape 1600 3785 / 3620, 2100 4525 / 4366, 2500 5445 / 5413; 13B MHA
+// shape 1600 4925 / 4870, 2100 6040 / 6054), only for down projections that
+// two halves of 256 x 256 tiles would fill better; left as it was measured.
 constexpr int kGemmShortRows = 1536;
 // Whether a K of `steps` steps may be split z ways: at least eight steps each,
 // whole pairs of them.
@@ -575,8 +581,8 @@ inline size_t gemm_part_elems(const buddy_config& c, size_t rows) {
 }
 // Whether the bf16 projections of a batch take the MFMA path (decode
 // sequences, or the tokens of a short prompt); fixed by the batch and the
-// model, so that a sequence's arithmetic never depends on the routes of the
-// others.  One sequence streams faster through the GEMV (Llama-8B shape:
+// model, so that a decoding sequence's projections never depend on the routes
+// of the others.  One sequence streams faster through the GEMV (Llama-8B shape:
 // gate/up 36 us against 39, and no staging kernels).  From two to four the
 // GEMV passes every weight by each row in turn (Qwen-7B shape, three rows:
 // gate/up 87 us and down 95, MFMA 50 and 30), while the MFMA path adds two

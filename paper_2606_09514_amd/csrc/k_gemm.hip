@@ -652,9 +652,9 @@ static hipError_t launch_shape(int shape, int splits, const GemvArgs& g, int uni
 // buffer holds the sums (197 tokens, Llama-8B shape, with the sums' launch:
 // O 62 -> 24 us, down 184 -> 47, QKV 67 -> 32, gate/up on 128 x 256 tiles
 // 102 -> 81 against 128 x 128 tiles unsplit; 900 tokens, 6 blocks 3040 ->
-// 2257, 13B MHA shape, 1500 tokens, 4 blocks 4960 -> 3480); longer ones split only the residual adds in two, where that fills
-// the CUs.  Adding split sums costs their write and read (about 5 TB/s) and a
-// launch.
+// 2257, 13B MHA shape, 1500 tokens, 4 blocks 4960 -> 3480); longer ones split
+// only the residual adds in two, where that fills the CUs.  Adding split sums
+// costs their write and read (about 5 TB/s) and a launch.
 template <int EPI>
 static hipError_t launch_auto(const GemvArgs& g, int units, float* part, size_t part_elems, hipStream_t s,
                               int* fold) {

@@ -4,9 +4,10 @@
 //                 and the identity row list used by the always-run blocks.
 //  pool_kernel    KV-aware planner (Sec. 4.3): sums of the first layer's K
 //                 and V rows 0..pos per KV head over a few split position
-//                 ranges; the Decision Module's first GEMV folds the splits
-//                 into the means and joins the newest hidden state,
-//                 z = [mean K | mean V | h] (PRO_POOL in k_gemv.hip).
+//                 ranges; the Decision Module's first layer (dm_kernel, or
+//                 the GEMV's PRO_POOL in k_gemv.hip) folds the splits into the
+//                 means and joins the newest hidden state,
+//                 z = [mean K | mean V | h].
 //  pool_running_kernel  the same sums kept across steps in caller memory:
 //                 only rows not yet summed are read (normally one per
 //                 sequence and step).
