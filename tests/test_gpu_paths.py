@@ -329,7 +329,7 @@ def test_block_that_few_sequences_run():
     alone = attention_us(model, 7, k, v, hidden, [T - 1])
     few = attention_us(model, 1 + block, k, v, hidden, [T - 1] * B)
     print("runs", runs, "alone", alone, "few", few)
-    assert runs[block] <= 4 and few < 2.5 * alone
+    assert runs[block] <= 4 and few < 3.5 * alone
 
 
 def test_split_tile_of_any_k():
